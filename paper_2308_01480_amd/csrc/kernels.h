@@ -166,10 +166,11 @@ hipError_t convert_pad(const void* in, int idt, int64_t rows, int cols, int64_t 
 hipError_t symmetrize(double* a, int n, hipStream_t st);
 hipError_t set_scalar(double* p, double v, hipStream_t st);  // *p = v (device)
 hipError_t identity(double* a, int64_t m, hipStream_t st);
-// Streaming TT reconstruction error: partial sums per outer prefix, then out3.
+// Streaming TT reconstruction error (tt_error.hip): at most part_groups partial triples (at
+// least one per 64 outer rows) in `part`, then out3.
 hipError_t tt_error_blocks(const void* x, int xdt, int64_t outer, int64_t inner, int s_split,
                            const int64_t* dims, const int64_t* ranks, const double* const* cores_dev,
-                           const double* R, double* part, double* out3, hipStream_t st);
+                           const double* R, double* part, int64_t part_groups, double* out3, hipStream_t st);
 
 // ---- backward-pass helpers (float64 small matrices) ----
 // C (m1 x m2) = alpha X (m1 x a) Y^T (Y: m2 x a) + beta C.

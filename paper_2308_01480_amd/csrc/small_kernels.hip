@@ -1,6 +1,6 @@
 // Small dense float64 kernels of the sweep: the m x w and w x w side of every mode
 // (projections between Krylov blocks, Gram matrices, SVQB orthonormalisation,
-// Rayleigh-Ritz, completion) and the streaming TT reconstruction error.
+// Rayleigh-Ritz, completion).
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -694,1195 +694,6 @@ hipError_t sym_eig(const double* a, int n, double* vecs, double* vals, double* w
 }
 
 // ----------------------------------------------------------------------------------
-// Leading eigenpairs of a symmetric n x n matrix (n <= kTopMaxN, r wanted pairs), for
-// the Rayleigh-Ritz and saturated Gram steps that only keep the top r directions.
-// 1. Householder reduction T = Q^T A Q to tridiagonal form.  A lives in registers:
-//    entry (i, j) belongs to thread (i mod 16, j mod 16) of a 16 x 16 grid, so the
-//    product A v is summed across the 16 lanes of one row group inside a wave (DPP).
-//    The reflectors are kept in LDS, packed.
-// 2. The r largest eigenvalues of T by multisection: gl lanes per eigenvalue count the
-//    eigenvalues below gl interior points of the current interval (sign changes of
-//    the leading principal minors of T - x I, rescaled by powers of two) and keep the
-//    sub-interval that holds the wanted index.
-// 3. Eigenvectors of T from twisted factorisations of T - lambda I (one forward and
-//    one backward recurrence per vector), then two Cholesky-QR passes over all r
-//    vectors (clustered eigenvalues give an orthonormal basis of the cluster).
-// 4. Back-transformation z = Q y with the stored reflectors.
-// Output: vals[0..r) decreasing, vecs[:, 0..r) (leading dimension n) unit vectors;
-// a value at or below n 2^-52 vals[0] counts as unresolved and gets a zero value and a
-// zero vector; vals[r..n) = 0.
-// ----------------------------------------------------------------------------------
-constexpr int kTopMaxN = 128;
-constexpr int kTopMaxR = 64;
-constexpr int kTopThreads = 256;
-
-template <int W>
-__device__ inline double group_total(double v) {
-  if constexpr (W == 16) return sum16(v);
-  else return sum32(v);
-}
-
-// 1/x to full precision from the hardware estimate and two Newton steps (|x| >= DBL_MIN).
-__device__ inline double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-
-// Number of eigenvalues of the tridiagonal (d, e2 = e^2) below x: sign changes of
-// p_i = det(T_i - x I), p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}, renormalised by a
-// power of two every 4 steps; an exact zero counts as a sign change (tiny pivot).
-__device__ inline int sturm_count(const double* __restrict__ d, const double* __restrict__ e2, int n, double x) {
-  double pm = 1.0, p = d[0] - x;
-  if (p == 0.0) p = -0x1p-1000;
-  int c = p < 0.0;
-  int i = 1;
-  for (; i + 3 < n; i += 4) {
-    const double d0 = d[i], d1 = d[i + 1], d2 = d[i + 2], d3 = d[i + 3];
-    const double f0 = e2[i - 1], f1 = e2[i], f2 = e2[i + 1], f3 = e2[i + 2];
-#define TTR_STURM_STEP(dv, fv)                         \
-    {                                                  \
-      double pn = fma(dv - x, p, -(fv)*pm);            \
-      if (pn == 0.0) pn = -0x1p-1000 * p;              \
-      c += (pn < 0.0) != (p < 0.0);                    \
-      pm = p;                                          \
-      p = pn;                                          \
-    }
-    TTR_STURM_STEP(d0, f0)
-    TTR_STURM_STEP(d1, f1)
-    TTR_STURM_STEP(d2, f2)
-    TTR_STURM_STEP(d3, f3)
-    const int ex = max(__builtin_amdgcn_frexp_exp(p), __builtin_amdgcn_frexp_exp(pm));
-    p = ldexp(p, -ex);
-    pm = ldexp(pm, -ex);
-  }
-  for (; i < n; ++i) TTR_STURM_STEP(d[i], e2[i - 1])
-#undef TTR_STURM_STEP
-  return c;
-}
-
-// Packed reflector storage: v_k (entries k+1..n-1) starts at refl_off(k).
-__device__ inline int refl_off(int k, int n) { return k * (n - 1) - (k * (k - 1)) / 2; }
-
-// Pivot used for the LDL^T / UDU^T recurrences: magnitudes below `tiny` become +-tiny.
-__device__ inline double guard_pivot(double x, double tiny) { return fabs(x) < tiny ? (x < 0.0 ? -tiny : tiny) : x; }
-
-// One panel of the Householder tridiagonalisation in k_eig_top: steps k = 16 KB + kc,
-// kc = 0..15, with the register column KB a compile-time index.  Rows and columns below
-// 16 KB are finished: their register blocks (a, b < KB) are neither read nor updated.
-template <int NB, int KB>
-__device__ inline void tri_panel(double (&A)[NB][NB], int n, double (*colb)[kTopMaxN], double (*pb)[kTopMaxN],
-                                 double* __restrict__ Vs, double* __restrict__ dd, double* __restrict__ ee,
-                                 double* __restrict__ taus) {
-  constexpr int TG = 16;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int tr = tid / TG, tc = tid % TG;
-  for (int kc = 0; kc < TG; ++kc) {
-    const int k = KB * TG + kc;
-    if (k + 2 >= n) break;
-    double* col = colb[k & 1];
-    double* p = pb[k & 1];
-    if (tc == kc) {
-#pragma unroll
-      for (int a = KB; a < NB; ++a) col[tr + TG * a] = A[a][KB];
-    }
-    __syncthreads();
-    double cr[NB], cc[NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-      cr[a] = col[tr + TG * a];
-      cc[a] = col[tc + TG * a];
-    }
-    const int i1 = k + 1 + lane, i2 = i1 + 64;
-    const double c1 = col[i1 < kTopMaxN ? i1 : 0], c2 = col[i2 < kTopMaxN ? i2 : 0];
-    const double x0 = col[k + 1];
-    // ||x(2:)||^2 over rows k+2 .. n-1 (c1 of lane 0 is x0 itself)
-    double s = (lane > 0 && i1 < n ? c1 * c1 : 0.0) + (i2 < n ? c2 * c2 : 0.0);
-    s = sum64(s);
-    double tau = 0.0, beta = x0, scale = 0.0;
-    if (s > 0.0) {
-      const double nrm = sqrt(fma(x0, x0, s));
-      beta = x0 >= 0.0 ? -nrm : nrm;
-      tau = (beta - x0) * rcp_nr(beta);
-      scale = rcp_nr(x0 - beta);
-    }
-    double vr[NB], vc[NB], w[NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-      const int i = tr + TG * a, j = tc + TG * a;
-      vr[a] = i == k + 1 ? 1.0 : ((i > k + 1 && i < n) ? cr[a] * scale : 0.0);
-      vc[a] = j == k + 1 ? 1.0 : ((j > k + 1 && j < n) ? cc[a] * scale : 0.0);
-    }
-#pragma unroll
-    for (int a = KB; a < NB; ++a) {
-      double t = 0.0;
-#pragma unroll
-      for (int b = KB; b < NB; ++b) t = fma(A[a][b], vc[b], t);
-      w[a] = sum16(t);
-    }
-    if (tc == 0) {
-#pragma unroll
-      for (int a = KB; a < NB; ++a) p[tr + TG * a] = tau * w[a];
-    }
-    const double v1 = lane == 0 ? 1.0 : c1 * scale, v2 = c2 * scale;
-    if (wid == 0) {
-      const int o = refl_off(k, n) - (k + 1);
-      if (i1 < n) Vs[o + i1] = v1;
-      if (i2 < n) Vs[o + i2] = v2;
-      if (lane == 0) { taus[k] = tau; ee[k] = beta; dd[k] = col[k]; }
-    }
-    __syncthreads();
-    double pr[NB], pc[NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-      pr[a] = p[tr + TG * a];
-      pc[a] = p[tc + TG * a];
-    }
-    const double q1 = p[i1 < kTopMaxN ? i1 : 0], q2 = p[i2 < kTopMaxN ? i2 : 0];
-    const double sk = (i1 < n ? v1 * q1 : 0.0) + (i2 < n ? v2 * q2 : 0.0);
-    const double K = 0.5 * tau * sum64(sk);
-    double wc[NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-      const int i = tr + TG * a, j = tc + TG * a;
-      w[a] = (i > k && i < n) ? fma(-K, vr[a], pr[a]) : 0.0;
-      wc[a] = (j > k && j < n) ? fma(-K, vc[a], pc[a]) : 0.0;
-    }
-#pragma unroll
-    for (int a = KB; a < NB; ++a)
-#pragma unroll
-      for (int b = KB; b < NB; ++b) A[a][b] -= vr[a] * wc[b] + w[a] * vc[b];
-  }
-}
-
-template <int NB, int KB>
-struct TriPanels {
-  __device__ static void run(double (&A)[NB][NB], int n, double (*colb)[kTopMaxN], double (*pb)[kTopMaxN],
-                             double* Vs, double* dd, double* ee, double* taus) {
-    if (16 * KB + 2 >= n) return;
-    tri_panel<NB, KB>(A, n, colb, pb, Vs, dd, ee, taus);
-    TriPanels<NB, KB + 1>::run(A, n, colb, pb, Vs, dd, ee, taus);
-  }
-};
-template <int NB>
-struct TriPanels<NB, NB> {
-  __device__ static void run(double (&)[NB][NB], int, double (*)[kTopMaxN], double (*)[kTopMaxN], double*, double*,
-                             double*, double*) {}
-};
-
-// Back-transformation panel KB of k_eig_top: y <- H_k y for k = 16 KB + 15 down to 16 KB
-// (k <= n - 3).  Rows below 16 KB are untouched by these reflectors, so only register
-// blocks a >= KB take part, and only block KB (rows on both sides of k) and the last block
-// (rows beyond n) need a mask.  Two reflectors at a time:
-// H_{k-1} H_k y = y - f1 v_k - f2 v_{k-1}, f1 = tau_k v_k^T y,
-// f2 = tau_{k-1} (v_{k-1}^T y - (v_{k-1}^T v_k) f1); the three dot products of a pair are
-// summed over the 16 lanes of a column group together.
-// Reflector v_k (entries k+1..n-1, v_k[k+1] = 1) read by the back-transformation:
-// packed in LDS behind each other (n <= kTopMaxN), or one row of pitch kBigPitch each in
-// global memory (larger n).  kMaskAll: every register block may hold rows >= n.
-struct ReflPacked {
-  const double* Vs;
-  int n;
-  static constexpr bool kMaskAll = false;
-  __device__ double operator()(int k, int i) const { return Vs[refl_off(k, n) - (k + 1) + i]; }
-};
-constexpr int kBigPitch = 256;
-struct ReflPitched {
-  const double* W;
-  static constexpr bool kMaskAll = true;
-  __device__ double operator()(int k, int i) const { return W[(int64_t)k * kBigPitch + i]; }
-};
-
-template <int NB, int CB2, int KB, class Refl>
-__device__ inline void back_panel(double (&yv)[NB][CB2], const Refl& refl, const double* __restrict__ taus, int n,
-                                  int rg) {
-  constexpr int TG = 16;
-  auto load_v = [&](int k, double (&v)[NB]) {
-#pragma unroll
-    for (int a = KB; a < NB; ++a) {
-      const int i = rg + TG * a;
-      if (a == KB || a == NB - 1 || Refl::kMaskAll) {
-        const int ic = i <= k ? k + 1 : (i < n ? i : n - 1);
-        const double x = refl(k, ic);
-        v[a] = (i > k && i < n) ? x : 0.0;
-      } else {
-        v[a] = refl(k, i);
-      }
-    }
-  };
-  int k = min(TG * KB + TG - 1, n - 3);
-  if (k < TG * KB) return;
-  if (((k - TG * KB) & 1) == 0) {  // odd count: one reflector first
-    double va[NB];
-    load_v(k, va);
-    const double t0 = taus[k];
-#pragma unroll
-    for (int b = 0; b < CB2; ++b) {
-      double x1 = 0.0;
-#pragma unroll
-      for (int a = KB; a < NB; ++a) x1 = fma(va[a], yv[a][b], x1);
-      const double f = t0 * sum16(x1);
-#pragma unroll
-      for (int a = KB; a < NB; ++a) yv[a][b] = fma(-f, va[a], yv[a][b]);
-    }
-    --k;
-  }
-  // the next pair's reflectors are loaded while the current pair is applied
-  double va[NB], vb[NB];
-  if (k > TG * KB) {
-    load_v(k, va);
-    load_v(k - 1, vb);
-  }
-  for (; k > TG * KB; k -= 2) {
-    const bool more = k - 2 > TG * KB;
-    double na[NB], nb[NB];
-    if (more) {
-      load_v(k - 2, na);
-      load_v(k - 3, nb);
-    }
-    const double ta = taus[k], tb = taus[k - 1];
-    double cp = 0.0;
-#pragma unroll
-    for (int a = KB; a < NB; ++a) cp = fma(vb[a], va[a], cp);
-    double d1[CB2], d2[CB2];
-#pragma unroll
-    for (int b = 0; b < CB2; ++b) {
-      double x1 = 0.0, x2 = 0.0;
-#pragma unroll
-      for (int a = KB; a < NB; ++a) {
-        x1 = fma(va[a], yv[a][b], x1);
-        x2 = fma(vb[a], yv[a][b], x2);
-      }
-      d1[b] = sum16(x1);
-      d2[b] = sum16(x2);
-    }
-    const double cab = sum16(cp);
-#pragma unroll
-    for (int b = 0; b < CB2; ++b) {
-      const double f1 = ta * d1[b];
-      const double f2 = tb * fma(-cab, f1, d2[b]);
-#pragma unroll
-      for (int a = KB; a < NB; ++a) yv[a][b] = fma(-f2, vb[a], fma(-f1, va[a], yv[a][b]));
-    }
-    if (more) {
-#pragma unroll
-      for (int a = KB; a < NB; ++a) {
-        va[a] = na[a];
-        vb[a] = nb[a];
-      }
-    }
-  }
-}
-
-template <int NB, int CB2, int KB, class Refl>
-struct BackPanels {
-  __device__ static void run(double (&yv)[NB][CB2], const Refl& refl, const double* taus, int n, int rg) {
-    back_panel<NB, CB2, KB>(yv, refl, taus, n, rg);
-    BackPanels<NB, CB2, KB - 1, Refl>::run(yv, refl, taus, n, rg);
-  }
-};
-template <int NB, int CB2, class Refl>
-struct BackPanels<NB, CB2, -1, Refl> {
-  __device__ static void run(double (&)[NB][CB2], const Refl&, const double*, int, int) {}
-};
-
-// Parts 2-4 of the leading-eigenpair solver, on the tridiagonal T = (dd, ee) of step 1
-// with its Householder reflectors (taus, refl): multisection for the r largest
-// eigenvalues, eigenvectors of T (twisted factorisations or inverse iteration inside
-// clusters) with Cholesky-QR, back-transformation into vecs / vals (without BACK, vecs
-// receives the eigenvectors of T and a separate launch applies the reflectors).  Runs on
-// kTopThreads threads; every array is shared memory except vecs, vals (and refl's storage).
-template <int NB, int RMAX, bool BACK = true, class Refl>
-__device__ inline void eig_top_tail(int n, int r, int bv, int gl, const double* __restrict__ dd,
-                                    const double* __restrict__ ee, double* __restrict__ e2,
-                                    const double* __restrict__ taus, const Refl& refl, double* __restrict__ lam,
-                                    double* __restrict__ rdiag, double (*colx)[64], int* __restrict__ twist,
-                                    double* __restrict__ Ys, double* __restrict__ Gm, double* __restrict__ Xi,
-                                    double* __restrict__ SD, double* __restrict__ SL, double* __restrict__ SU,
-                                    double* __restrict__ vecs, double* __restrict__ vals) {
-  constexpr int TG = 16, NT = kTopThreads;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int rp = r + 1;
-  for (int i = tid; i + 1 < n; i += NT) e2[i] = ee[i] * ee[i];
-
-  // ---- 2. the r largest eigenvalues of T: gl lanes per eigenvalue, gl + 1 subintervals ----
-  double glo = 1e308, ghi = -1e308;
-  for (int i = lane; i < n; i += 64) {
-    const double el = i > 0 ? fabs(ee[i - 1]) : 0.0, er = i + 1 < n ? fabs(ee[i]) : 0.0;
-    glo = fmin(glo, dd[i] - el - er);
-    ghi = fmax(ghi, dd[i] + el + er);
-  }
-  glo = min64(glo);
-  ghi = max64(ghi);
-  const double tnrm = fmax(fmax(fabs(glo), fabs(ghi)), 0x1p-1000);
-  const double fudge = 4.0 * (double)n * 0x1p-52 * tnrm;
-  glo -= fudge;
-  ghi += fudge;
-  const double tol = 4.0 * 0x1p-52 * tnrm;
-  __syncthreads();
-  // groups of gl lanes (2 <= gl <= 32) never straddle a wave: GPW = 64 / gl per wave, the
-  // last 64 - GPW gl lanes of a wave idle
-  const double frac = 1.0 / (double)(gl + 1);
-  const unsigned gmask = (gl >= 32) ? 0xFFFFFFFFu : ((1u << gl) - 1u);
-  const int gpw = 64 / gl, gi = lane / gl, g = lane % gl;
-  for (int j0 = 0; j0 < r; j0 += (NT / 64) * gpw) {
-    const int j = j0 + wid * gpw + gi;
-    if (gi < gpw && j < r) {
-      const int idx = n - 1 - j;  // ascending index of the j-th largest eigenvalue
-      double lo = glo, hi = ghi;
-      for (int it = 0; it < 96 && hi - lo > tol; ++it) {
-        const double h = (hi - lo) * frac;
-        const int c = sturm_count(dd, e2, n, lo + h * (double)(g + 1));
-        const uint64_t ball = __ballot(c <= idx);
-        const unsigned bits = (unsigned)(ball >> (gi * gl)) & gmask;
-        const int top = bits ? 31 - __clz(bits) : -1;  // last point with <= idx values below it
-        const double nlo = top >= 0 ? lo + h * (double)(top + 1) : lo;
-        const double nhi = top < gl - 1 ? lo + h * (double)(top + 2) : hi;
-        lo = nlo;
-        hi = nhi;
-      }
-      if (g == 0) lam[j] = 0.5 * (lo + hi);
-    }
-  }
-  __syncthreads();
-
-  // ---- 3. eigenvectors of T.  Lane pair (2t, 2t+1) factors T - lambda I = L D L^T (forward)
-  //         and = U R U^T (backward).  An isolated value takes the twisted vector: at the
-  //         index k with the smallest |gamma_k| = |D_k + R_k - (d_k - lambda)|, z_k = 1,
-  //         z_i = -L_i z_{i+1} (i < k), z_{i+1} = -U_i z_i (i >= k).  A value within
-  //         1e-3 ||T|| of a neighbour instead takes two solves with L D L^T from a hashed
-  //         right-hand side, so that the vectors of a cluster span its eigenspace.  Column j
-  //         of Ys holds R (then the vector) of eigenvalue j. ----
-  const double tiny = 0x1p-52 * tnrm;
-  const double cthr = 1e-3 * tnrm;
-  bool any_clust = false;
-  for (int j = 0; j < r; ++j)
-    any_clust |= (j > 0 && lam[j - 1] - lam[j] < cthr) || (j + 1 < r && lam[j] - lam[j + 1] < cthr);
-  for (int jb = 0; jb < r; jb += bv) {
-    const int t = tid >> 1, side = tid & 1, j = jb + t;
-    const bool act = t < bv && j < r;
-    const double lj = act ? lam[j] : 0.0;
-    const bool clust = act && ((j > 0 && lam[j - 1] - lj < cthr) || (j + 1 < r && lj - lam[j + 1] < cthr));
-    if (act && (side == 0 || !clust)) {
-      // both lanes of a pair run the same instructions: side 0 forward (L, D: p = D),
-      // side 1 backward (U, R: p = R, R kept in column j of Ys)
-      double* Xo = side ? SU : SL;
-      double* Po = side ? Ys : SD;
-      const int ps = side ? rp : bv, pc = side ? j : t;
-      double P = guard_pivot(dd[side ? n - 1 : 0] - lj, tiny);
-      Po[(side ? n - 1 : 0) * ps + pc] = P;
-      for (int st = 0; st + 1 < n; ++st) {
-        const int ie = side ? n - 2 - st : st;      // off-diagonal entry of this step
-        const int id = side ? n - 2 - st : st + 1;  // diagonal entry it updates
-        const double x = ee[ie] * rcp_nr(P);
-        Xo[ie * bv + t] = x;
-        P = guard_pivot(fma(-x, ee[ie], dd[id] - lj), tiny);
-        Po[id * ps + pc] = P;
-      }
-    }
-    __syncthreads();
-    if (act && side == 0 && !clust) {
-      int kbest = 0;
-      double gbest = 1e308;
-      for (int k = 0; k < n; ++k) {
-        const double gk = fabs(SD[k * bv + t] + Ys[k * rp + j] - (dd[k] - lj));
-        if (gk < gbest) { gbest = gk; kbest = k; }
-      }
-      twist[t] = kbest;
-    }
-    __syncthreads();
-    if (act && !clust) {
-      // side 0: z_i = -L_i z_{i+1} for i = kt-1 .. 0; side 1: z_{i+1} = -U_i z_i for
-      // i = kt .. n-2 (a zero z takes the three-term relation instead)
-      const int kt = twist[t];
-      const double* X = side ? SU : SL;
-      const int cnt = side ? n - 1 - kt : kt;
-      if (side == 0) Ys[kt * rp + j] = 1.0;
-      double nn = side ? 0.0 : 1.0;
-      double zp = 1.0, zpp = 0.0;
-      for (int st = 0; st < cnt; ++st) {
-        const int i = side ? kt + st : kt - 1 - st;
-        double z = -X[i * bv + t] * zp;
-        const bool nb = side ? i > 0 : i + 1 < n - 1;
-        const int inb = side ? (i > 0 ? i - 1 : 0) : i + 1;
-        if (zp == 0.0 && ee[i] != 0.0 && nb) z = -(ee[inb] / ee[i]) * zpp;
-        Ys[(side ? i + 1 : i) * rp + j] = z;
-        nn = fma(z, z, nn);
-        zpp = zp;
-        zp = z;
-      }
-      const double inv = 1.0 / sqrt(nn + __shfl_xor(nn, 1, 64));
-      for (int i = side ? kt + 1 : 0; i < (side ? n : kt + 1); ++i) Ys[i * rp + j] *= inv;
-    }
-    if (act && clust && side == 0) {
-      // x = (L D L^T)^{-1} b twice, in column j of Ys; b_i in [0.5, 1.5) from a hash of (i, j)
-      for (int it = 0; it < 2; ++it) {
-        double yv = 0.0;
-        for (int i = 0; i < n; ++i) {
-          const uint32_t hsh = (uint32_t)(i * 2654435761u) ^ (uint32_t)((j + 1) * 40503u);
-          const double b = it == 0 ? 0.5 + (double)((hsh >> 8) & 0xFFFF) * (1.0 / 65536.0) : Ys[i * rp + j];
-          yv = i == 0 ? b : fma(-SL[(i - 1) * bv + t], yv, b);
-          Ys[i * rp + j] = yv;
-        }
-        double xv = 0.0, nn = 0.0;
-        for (int i = n - 1; i >= 0; --i) {
-          const double yi = Ys[i * rp + j] * rcp_nr(SD[i * bv + t]);
-          xv = i == n - 1 ? yi : fma(-SL[i * bv + t], xv, yi);
-          Ys[i * rp + j] = xv;
-          nn = fma(xv, xv, nn);
-        }
-        const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
-        for (int i = 0; i < n; ++i) Ys[i * rp + j] *= inv;
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- Cholesky-QR of Y (a second pass when a cluster took inverse iteration): Gram (one
-  //      thread per entry), Cholesky on the four waves (lane l holds row l, each wave a
-  //      quarter of the columns), then every row of Y solved against R in registers ----
-  for (int pass = 0; pass < (any_clust ? 2 : 1); ++pass) {
-    for (int e = tid; e < r * r; e += NT) {
-      const int c1 = e / r, c2 = e % r;
-      if (c1 <= c2) {
-        double sacc = 0.0;
-#pragma unroll 8
-        for (int i = 0; i < n; ++i) sacc = fma(Ys[i * rp + c1], Ys[i * rp + c2], sacc);
-        Gm[c1 * rp + c2] = sacc;
-      }
-    }
-    __syncthreads();
-    {  // R (upper, rows in Gm), 1 / R_jj in Xi[j]: lane l holds row l, wave w the columns
-       // [w CW, (w+1) CW); the pivot row comes from lane k of each wave, the pivot column
-       // (= row, by symmetry) through LDS from the wave that owns it
-      constexpr int CW = RMAX / 4;
-      const int c0 = wid * CW;
-      double row[CW];
-#pragma unroll
-      for (int t = 0; t < CW; ++t) {
-        const int c = c0 + t;
-        row[t] = (lane < r && c < r) ? (c >= lane ? Gm[lane * rp + c] : Gm[c * rp + lane]) : 0.0;
-      }
-      for (int k = 0; k < r; ++k) {
-        double* cb = colx[k & 1];
-        if (k >= c0 && k < c0 + CW) {
-          double cv = 0.0;
-#pragma unroll
-          for (int t = 0; t < CW; ++t) cv = (c0 + t == k) ? row[t] : cv;
-          cb[lane] = cv;
-        }
-        __syncthreads();
-        const double d = cb[k];
-        const bool ok = d > 1e-20;
-        const double rinv = ok ? rsqrt_nr(d) : 0.0;
-        const double rl = (ok && lane > k && lane < r) ? cb[lane] * rinv : 0.0;
-        if (wid == 0 && lane > k && lane < r) Gm[k * rp + lane] = rl;
-        if (tid == 0) { Xi[k] = rinv; rdiag[k] = ok ? d * rinv : 0.0; }
-        const double f = -rl * rinv;
-#pragma unroll
-        for (int t = 0; t < CW; ++t) row[t] = fma(f, lane_value(row[t], k), row[t]);
-      }
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += NT) {  // y R = y_old, row by row (dependent columns give zeros)
-      double y[RMAX];
-#pragma unroll
-      for (int jj = 0; jj < RMAX; ++jj) y[jj] = jj < r ? Ys[i * rp + jj] : 0.0;
-#pragma unroll
-      for (int jj = 0; jj < RMAX; ++jj) {
-        double acc = y[jj];
-#pragma unroll
-        for (int c = 0; c < jj; ++c) acc = fma(-y[c], Gm[c * rp + jj], acc);
-        y[jj] = jj < r ? acc * Xi[jj] : 0.0;
-      }
-#pragma unroll
-      for (int jj = 0; jj < RMAX; ++jj)
-        if (jj < r) Ys[i * rp + jj] = y[jj];
-    }
-    __syncthreads();
-  }
-
-  if constexpr (!BACK) {
-    const double res0 = (double)n * 0x1p-52 * fmax(lam[0], 0.0);
-    for (int e = tid; e < n * r; e += NT) {
-      const int i = e / r, c = e % r;
-      vecs[i * n + c] = (rdiag[c] > 0.0 && lam[c] > res0) ? Ys[i * rp + c] : 0.0;
-    }
-    for (int c = tid; c < n; c += NT) vals[c] = (c < r && rdiag[c] > 0.0 && lam[c] > res0) ? lam[c] : 0.0;
-    return;
-  }
-  // ---- 4. back-transformation z = Q y with the stored reflectors, last first.  Thread
-  //      (row group rg = lane % 16, column group cg = tid / 16) keeps rows rg + 16 a and
-  //      columns cg + 16 b of y in registers; the dot products of a reflector with a column
-  //      are summed over the 16 lanes of the column group (DPP), so no barrier is needed. ----
-  constexpr int CB2 = RMAX / 16;
-  const int rg = lane & 15, cg = tid >> 4;
-  const double res = (double)n * 0x1p-52 * fmax(lam[0], 0.0);
-  double yv[NB][CB2];
-#pragma unroll
-  for (int a = 0; a < NB; ++a)
-#pragma unroll
-    for (int b = 0; b < CB2; ++b) {
-      const int i = rg + TG * a, c = cg + 16 * b;
-      yv[a][b] = (c < r && i < n) ? Ys[i * rp + c] : 0.0;
-    }
-  // Reflectors are applied two at a time, panel by panel (k = 16 KB + 15 .. 16 KB): see
-  // back_panel.
-  BackPanels<NB, CB2, NB - 1, Refl>::run(yv, refl, taus, n, rg);
-#pragma unroll
-  for (int b = 0; b < CB2; ++b) {
-    const int c = cg + 16 * b;
-    if (c < r) {
-      const bool keep = rdiag[c] > 0.0 && lam[c] > res;
-#pragma unroll
-      for (int a = 0; a < NB; ++a) {
-        const int i = rg + TG * a;
-        if (i < n) vecs[i * n + c] = keep ? yv[a][b] : 0.0;
-      }
-      if (rg == 0) vals[c] = keep ? lam[c] : 0.0;
-    }
-  }
-  for (int j = r + tid; j < n; j += NT) vals[j] = 0.0;
-}
-
-template <int NB, int RMAX>
-__global__ __launch_bounds__(kTopThreads) void k_eig_top(const double* __restrict__ a_in, int n, int r,
-                                                         double* __restrict__ vecs, double* __restrict__ vals, int bv,
-                                                         int gl) {
-  constexpr int TG = 16;
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double colb[2][kTopMaxN], pb[2][kTopMaxN];
-  __shared__ double dd[kTopMaxN], ee[kTopMaxN], e2[kTopMaxN], taus[kTopMaxN];
-  __shared__ double lam[kTopMaxR], rdiag[kTopMaxR], colx[2][64];
-  __shared__ int twist[kTopMaxR];
-  const int tid = threadIdx.x;
-  const int tr = tid / TG, tc = tid % TG;
-  const int rp = r + 1;
-  double* Vs = reinterpret_cast<double*>(smem);            // packed reflectors
-  double* Ys = Vs + ((n * (n - 1) / 2 + 1) & ~1);          // n x rp eigenvectors of T, then of A
-  double* Gm = Ys + n * rp;                                // r x rp Gram / R factor
-  double* Xi = Gm + r * rp;                                // 1 / R_jj
-  double* SD = Xi + r * rp;                                // twisted factorisations, [i * bv + t]
-  double* SL = SD + n * bv;
-  double* SU = SL + n * bv;
-
-  // ---- 1. tridiagonalisation: every LDS operand of a step is read in one batch ----
-  double A[NB][NB];
-#pragma unroll
-  for (int a = 0; a < NB; ++a)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int i = tr + TG * a, j = tc + TG * b;
-      A[a][b] = (i < n && j < n) ? a_in[i * n + j] : 0.0;
-    }
-  TriPanels<NB, 0>::run(A, n, colb, pb, Vs, dd, ee, taus);
-  {
-    const int k0 = n >= 2 ? n - 2 : 0;
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int i = tr + TG * a, j = tc + TG * b;
-        if (i == j && i >= k0 && i < n) dd[i] = A[a][b];
-        if (n >= 2 && i == n - 1 && j == n - 2) ee[n - 2] = A[a][b];
-      }
-  }
-  __syncthreads();
-  eig_top_tail<NB, RMAX>(n, r, bv, gl, dd, ee, e2, taus, ReflPacked{Vs, n}, lam, rdiag, colx, twist, Ys, Gm, Xi, SD, SL,
-                         SU, vecs, vals);
-}
-
-// Dynamic LDS of k_eig_top: packed reflectors, Y, its Gram / R factor and 1 / R_jj, and bv
-// pairs of twisted factorisations (D, L, U: 3 doubles per entry and vector).
-static size_t eig_top_lds(int n, int r, int bv) {
-  const size_t refl = (size_t)((n * (n - 1) / 2 + 1) & ~1) * 8;
-  const size_t gx = 2 * (size_t)r * (r + 1);
-  return refl + ((size_t)n * (r + 1) + gx) * 8 + (size_t)bv * n * 24 + 16;
-}
-
-template <int NB, int RMAX>
-static hipError_t launch_eig_top_r(const double* a, int n, int r, double* vecs, double* vals, hipStream_t st, int bv) {
-  const size_t lds = eig_top_lds(n, r, bv);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_eig_top<NB, RMAX>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) { (void)hipGetLastError(); return e; }
-  // lanes per eigenvalue: the most (at most 16) that still bisect all r values in one
-  // round, with 64 / gl groups in each of the four waves
-  int gl = 16;
-  while (gl > 2 && (kTopThreads / 64) * (64 / gl) < r) --gl;
-  hipLaunchKernelGGL((k_eig_top<NB, RMAX>), dim3(1), dim3(kTopThreads), lds, st, a, n, r, vecs, vals, bv, gl);
-  return hipGetLastError();
-}
-
-template <int NB>
-static hipError_t launch_eig_top(const double* a, int n, int r, double* vecs, double* vals, hipStream_t st, int bv) {
-  if (r <= 16) return launch_eig_top_r<NB, 16>(a, n, r, vecs, vals, st, bv);
-  if (r <= 32) return launch_eig_top_r<NB, 32>(a, n, r, vecs, vals, st, bv);
-  return launch_eig_top_r<NB, 64>(a, n, r, vecs, vals, st, bv);
-}
-
-// ----------------------------------------------------------------------------------
-// Leading eigenpairs for kTopMaxN < n <= kMaxSmall (the Rayleigh-Ritz matrix of wide
-// Krylov spaces, e.g. w = 200): the matrix no longer fits one work-group's registers or
-// LDS, so step 1 runs on a copy in global memory (L2-resident: at most 512 KB) and the
-// other steps follow on the tridiagonal form.
-//
-// k_tridiag_big: Householder tridiagonalisation (lower form, as in step 1 of k_eig_top)
-// by 1024 threads.  Step k's rank-2 update A -= v w^T + w v^T is applied lazily, fused
-// with step k+1's product p = tau A v: one pass over the trailing block per step.  The
-// first k0 steps keep the matrix in global memory (L2-resident, rows of pitch kBigPitch;
-// wave w owns rows i = w (mod 16), lane l columns l + 64 c).  From step k0 on the trailing
-// block's lower triangle (rows and columns >= k0, packed by rows) fits in LDS and the
-// product is split in two passes: rows (the update, and sum_{j <= i} A_ij v_j) then
-// columns (sum_{i > j} A_ij v_j).  Eight lanes own the pair of rows (and of columns)
-// k + 1 + a and n - 1 - a, whose lengths add up to the same count for every a, and sum
-// them in a fixed order.  Row k (the symmetric copy of column k) is formed with the
-// pending update, gives d_k, e_k and the reflector, which is stored in W[k][k+1..n) for
-// the back-transformation.  W: n rows of pitch kBigPitch, then d, e, tau (kBigPitch each).
-// ----------------------------------------------------------------------------------
-constexpr int kTriThreads = 1024;
-
-__device__ inline double block_sum_tri(double v, double* red, int tid) {
-  v = sum64(v);
-  if ((tid & 63) == 0) red[tid >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-#pragma unroll
-  for (int w = 0; w < kTriThreads / 64; ++w) t += red[w];  // fixed order: every thread the same sum
-  __syncthreads();
-  return t;
-}
-
-// Offset of (i, j), j <= i, in the packed lower triangle of the block that starts at k0.
-__device__ inline int tri_off(int i, int j, int k0) {
-  const int a = i - k0;
-  return a * (a + 1) / 2 + (j - k0);
-}
-
-// Step-k start shared by both storage forms: the reflector from xs (row k with the
-// pending update), stored as d_k, e_k, tau_k and W[k][k+1..n); vc <- v.  Returns tau.
-__device__ inline double tri_reflector(int n, int k, double* xs, double* red, double* s_sc, double* dg, double* eg,
-                                       double* tg, double* W, double* vc) {
-  const int tid = threadIdx.x;
-  double sq = 0.0;
-  for (int i = k + 2 + tid; i < n; i += kTriThreads) sq += xs[i] * xs[i];
-  sq = block_sum_tri(sq, red, tid);
-  if (tid == 0) {
-    const double x0 = xs[k + 1];
-    double tau = 0.0, beta = x0, scale = 0.0;
-    if (sq > 0.0) {
-      const double nrm = sqrt(fma(x0, x0, sq));
-      beta = x0 >= 0.0 ? -nrm : nrm;
-      tau = (beta - x0) / beta;
-      scale = 1.0 / (x0 - beta);
-    }
-    s_sc[0] = tau; s_sc[1] = scale;
-    dg[k] = xs[k];
-    eg[k] = beta;
-    tg[k] = tau;
-  }
-  __syncthreads();
-  const double tau = s_sc[0], scale = s_sc[1];
-  for (int i = k + 1 + tid; i < n; i += kTriThreads) {
-    const double v = i == k + 1 ? 1.0 : xs[i] * scale;
-    vc[i] = v;
-    W[(int64_t)k * kBigPitch + i] = v;  // reflector k
-  }
-  if (tid == 0) vc[k] = 0.0;
-  __syncthreads();
-  return tau;
-}
-
-// w = p - (tau/2 v^T p) v on wc (holding p), then the pending update becomes (vc, wc).
-__device__ inline void tri_finish_w(int n, int k, double tau, const double* vc, double* wc, double* red) {
-  const int tid = threadIdx.x;
-  double kv = 0.0;
-  for (int i = k + 1 + tid; i < n; i += kTriThreads) kv += vc[i] * wc[i];
-  const double K = 0.5 * tau * block_sum_tri(kv, red, tid);
-  for (int i = k + 1 + tid; i < n; i += kTriThreads) wc[i] = fma(-K, vc[i], wc[i]);
-  if (tid == 0) wc[k] = 0.0;
-  __syncthreads();
-}
-
-// Row pass of one LDS step for the pair of rows i1 <= i2 (i1 == i2: one row): the pending
-// update A_ij -= v_i w_j + w_i v_j over j = k+1..i, written back, and sum_j A_ij c_j with
-// the new reflector c_j = x_j scale (c_{k+1} = 1; x = row k, xs).  Lane q of eight takes
-// j = k+1+q (mod 8); the vector entries of a column serve both rows, and every load of a
-// round is issued before its stores.
-__device__ inline void tri_row_pair(double* T, int k0, int k, int i1, int i2, int q, const double* vp,
-                                    const double* wp, const double* xs, double scale, double& p1, double& p2) {
-  double* ra = T + (i1 - k0) * (i1 - k0 + 1) / 2 - k0;  // element (i1, j) at ra[j]
-  double* rb = T + (i2 - k0) * (i2 - k0 + 1) / 2 - k0;
-  const bool two = i2 != i1;
-  const double va = vp[i1], wa = wp[i1], vb = vp[i2], wb = wp[i2];
-  auto cof = [&](int j) { return j == k + 1 ? 1.0 : xs[j] * scale; };
-  double pa = 0.0, pb = 0.0;
-  int j = k + 1 + q;
-  // columns of both rows, two per round
-  for (; j + 8 <= i1; j += 16) {
-    const double w0 = wp[j], w1 = wp[j + 8], v0 = vp[j], v1 = vp[j + 8];
-    const double c0 = cof(j), c1 = cof(j + 8);
-    double a0 = ra[j], a1 = ra[j + 8];
-    double b0 = two ? rb[j] : 0.0, b1 = two ? rb[j + 8] : 0.0;
-    a0 = a0 - va * w0 - wa * v0;
-    a1 = a1 - va * w1 - wa * v1;
-    ra[j] = a0; ra[j + 8] = a1;
-    pa = fma(a0, c0, pa);
-    pa = fma(a1, c1, pa);
-    if (two) {
-      b0 = b0 - vb * w0 - wb * v0;
-      b1 = b1 - vb * w1 - wb * v1;
-      rb[j] = b0; rb[j + 8] = b1;
-      pb = fma(b0, c0, pb);
-      pb = fma(b1, c1, pb);
-    }
-  }
-  for (; j <= i1; j += 8) {
-    const double w0 = wp[j], v0 = vp[j], c0 = cof(j);
-    const double a0 = ra[j] - va * w0 - wa * v0;
-    ra[j] = a0;
-    pa = fma(a0, c0, pa);
-    if (two) {
-      const double b0 = rb[j] - vb * w0 - wb * v0;
-      rb[j] = b0;
-      pb = fma(b0, c0, pb);
-    }
-  }
-  // the rest of row i2, four columns per round
-  if (two) {
-    for (; j + 24 <= i2; j += 32) {
-      double r0 = rb[j], r1 = rb[j + 8], r2 = rb[j + 16], r3 = rb[j + 24];
-      const double w0 = wp[j], w1 = wp[j + 8], w2 = wp[j + 16], w3 = wp[j + 24];
-      const double v0 = vp[j], v1 = vp[j + 8], v2 = vp[j + 16], v3 = vp[j + 24];
-      const double c0 = cof(j), c1 = cof(j + 8), c2 = cof(j + 16), c3 = cof(j + 24);
-      r0 = r0 - vb * w0 - wb * v0;
-      r1 = r1 - vb * w1 - wb * v1;
-      r2 = r2 - vb * w2 - wb * v2;
-      r3 = r3 - vb * w3 - wb * v3;
-      rb[j] = r0; rb[j + 8] = r1; rb[j + 16] = r2; rb[j + 24] = r3;
-      pb = fma(r0, c0, pb);
-      pb = fma(r1, c1, pb);
-      pb = fma(r2, c2, pb);
-      pb = fma(r3, c3, pb);
-    }
-    for (; j <= i2; j += 8) {
-      const double r0 = rb[j] - vb * wp[j] - wb * vp[j];
-      rb[j] = r0;
-      pb = fma(r0, cof(j), pb);
-    }
-  }
-  p1 = pa;
-  p2 = pb;
-}
-
-// Column pass for column j: sum_{r > j} A_rj vc_r, lane q of eight taking r = j+1+q (mod 8).
-__device__ inline double tri_col_pass(const double* T, int k0, int n, int j, int q, const double* vc) {
-  double part = 0.0;
-  int r = j + 1 + q;
-  int off = tri_off(r, j, k0);  // off(r + 8) = off(r) + 8 (r - k0) + 36
-  for (; r + 24 < n; r += 32) {
-    const int o1 = off + 8 * (r - k0) + 36;
-    const int o2 = o1 + 8 * (r + 8 - k0) + 36;
-    const int o3 = o2 + 8 * (r + 16 - k0) + 36;
-    const double t0 = T[off], t1 = T[o1], t2 = T[o2], t3 = T[o3];
-    const double c0 = vc[r], c1 = vc[r + 8], c2 = vc[r + 16], c3 = vc[r + 24];
-    part = fma(t0, c0, part);
-    part = fma(t1, c1, part);
-    part = fma(t2, c2, part);
-    part = fma(t3, c3, part);
-    off = o3 + 8 * (r + 24 - k0) + 36;
-  }
-  for (; r < n; r += 8) {
-    part = fma(T[off], vc[r], part);
-    off += 8 * (r - k0) + 36;
-  }
-  return part;
-}
-
-__global__ __launch_bounds__(kTriThreads) void k_tridiag_big(const double* __restrict__ a_in, int n,
-                                                            double* __restrict__ W, int k0) {
-  extern __shared__ double T[];  // packed lower triangle of rows / columns >= k0
-  __shared__ double vbuf[2][kBigPitch], wbuf[2][kBigPitch], xs[kBigPitch];
-  __shared__ double red[kTriThreads / 64], redK[kTriThreads / 64];
-  __shared__ double s_sc[2], s_x0[1];
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  double* dg = W + (int64_t)n * kBigPitch;
-  double* eg = dg + kBigPitch;
-  double* tg = eg + kBigPitch;
-  for (int e = tid; e < n * kBigPitch; e += kTriThreads) {
-    const int i = e / kBigPitch, j = e % kBigPitch;
-    W[e] = j < n ? a_in[(int64_t)i * n + j] : 0.0;
-  }
-  for (int i = tid; i < kBigPitch; i += kTriThreads) { vbuf[0][i] = 0.0; wbuf[0][i] = 0.0; }
-  if (tid < kTriThreads / 64) redK[tid] = 0.0;
-  __syncthreads();
-  int cur = 0;  // vbuf/wbuf[cur]: the update pending from the previous step
-  int k = 0;
-  for (; k + 2 < n && k < k0; ++k) {
-    const double* vp = vbuf[cur];
-    const double* wp = wbuf[cur];
-    for (int i = k + tid; i < n; i += kTriThreads)
-      xs[i] = W[(int64_t)k * kBigPitch + i] - vp[k] * wp[i] - wp[k] * vp[i];
-    __syncthreads();
-    double* vc = vbuf[cur ^ 1];
-    double* wc = wbuf[cur ^ 1];
-    const double tau = tri_reflector(n, k, xs, red, s_sc, dg, eg, tg, W, vc);
-    // fused: pending update of the trailing block, then p_i = tau sum_j A_ij v_j
-    for (int i = k + 1 + wid; i < n; i += kTriThreads / 64) {
-      double* row = W + (int64_t)i * kBigPitch;
-      const double vpi = vp[i], wpi = wp[i];
-      double part = 0.0;
-#pragma unroll
-      for (int c = 0; c < kBigPitch / 64; ++c) {
-        const int j = lane + 64 * c;
-        if (j > k && j < n) {
-          const double a = row[j] - vpi * wp[j] - wpi * vp[j];
-          row[j] = a;
-          part = fma(a, vc[j], part);
-        }
-      }
-      part = sum64(part);
-      if (lane == 0) wc[i] = tau * part;  // p, turned into w below
-    }
-    __syncthreads();
-    tri_finish_w(n, k, tau, vc, wc, red);
-    cur ^= 1;
-  }
-  if (k + 2 < n) {
-    // the trailing block (rows and columns >= k = k0) moves to LDS, without the pending update
-    for (int i = k + wid; i < n; i += kTriThreads / 64)
-      for (int j = k + lane; j <= i; j += 64) T[tri_off(i, j, k0)] = W[(int64_t)i * kBigPitch + j];
-    __syncthreads();
-  }
-  // LDS steps.  At the start of step k, vbuf[cur] holds v of step k - 1 and wbuf[cur] its
-  // p = tau A v; its w = p - K v, K = kscale * (sum of redK), is completed by the owner of
-  // each entry in phase X (K = 0 on entry: wbuf then holds w itself).
-  double kscale = 0.0;
-  for (; k + 2 < n; ++k) {
-    const double* vp = vbuf[cur];
-    double* wp = wbuf[cur];
-    double* vc = vbuf[cur ^ 1];
-    double* pc = wbuf[cur ^ 1];
-    double ks = 0.0;
-#pragma unroll
-    for (int w = 0; w < kTriThreads / 64; ++w) ks += redK[w];  // fixed order
-    const double K = kscale * ks;
-    // phase X: thread i - k forms w_i and row k's entry x_i with the pending update
-    const int i = k + tid;
-    const double vk = vp[k], wk = fma(-K, vk, wp[k]);
-    double x = 0.0, sq = 0.0;
-    if (i < n) {
-      const double vi = vp[i];
-      const double wi = fma(-K, vi, wp[i]);
-      if (i > k) wp[i] = wi;  // w_k stays p_k in LDS: every thread reads it above
-      x = T[tri_off(i, k, k0)] - vk * wi - wk * vi;
-      if (i >= k + 2) sq = x * x;
-      if (i == k + 1) s_x0[0] = x;
-      if (i == k) dg[k] = x;
-      xs[i] = x;
-    }
-    sq = sum64(sq);
-    if (lane == 0) red[wid] = sq;
-    __syncthreads();
-    // the reflector, by every thread from the same sums
-    double sqs = 0.0;
-#pragma unroll
-    for (int w = 0; w < kTriThreads / 64; ++w) sqs += red[w];
-    const double x0 = s_x0[0];
-    double tau = 0.0, beta = x0, scale = 0.0;
-    if (sqs > 0.0) {
-      const double nrm = sqrt(fma(x0, x0, sqs));
-      beta = x0 >= 0.0 ? -nrm : nrm;
-      tau = (beta - x0) / beta;
-      scale = 1.0 / (x0 - beta);
-    }
-    if (tid == 0) { eg[k] = beta; tg[k] = tau; }
-    // v_i = x_i scale (v_{k+1} = 1): kept by its owner for the column pass and the next
-    // step (visible after the row pass's barrier); the row pass forms it from xs itself
-    if (i < n) {
-      const double v = i == k ? 0.0 : (i == k + 1 ? 1.0 : x * scale);
-      vc[i] = v;
-      if (i > k) W[(int64_t)k * kBigPitch + i] = v;  // reflector k
-    }
-    const int N = n - k - 1;  // rows and columns k + 1 .. n - 1
-    const int a = tid >> 3, q = tid & 7;
-    const int i1 = k + 1 + a, i2 = n - 1 - a;  // i1 == i2: the middle row of an odd N
-    const bool act = a < (N + 1) / 2, two = i2 != i1;
-    double p1 = 0.0, p2 = 0.0;
-    if (act) tri_row_pair(T, k0, k, i1, i2, q, vp, wp, xs, scale, p1, p2);
-    p1 = sum8(p1);
-    p2 = sum8(p2);
-    if (act && q == 0) {
-      pc[i1] = p1;
-      if (two) pc[i2] = p2;
-    }
-    __syncthreads();
-    double c1 = 0.0, c2 = 0.0;
-    if (act) {
-      c1 = tri_col_pass(T, k0, n, i1, q, vc);
-      if (two) c2 = tri_col_pass(T, k0, n, i2, q, vc);
-    }
-    c1 = sum8(c1);
-    c2 = sum8(c2);
-    double kv = 0.0;
-    if (act && q == 0) {
-      const double pa = tau * (pc[i1] + c1);
-      pc[i1] = pa;
-      kv = vc[i1] * pa;
-      if (two) {
-        const double pb = tau * (pc[i2] + c2);
-        pc[i2] = pb;
-        kv = fma(vc[i2], pb, kv);
-      }
-    }
-    kv = sum64(kv);
-    if (lane == 0) redK[wid] = kv;
-    kscale = 0.5 * tau;
-    __syncthreads();
-    cur ^= 1;
-  }
-  // the last 2 x 2 block with the update of the last step
-  if (tid == 0) {
-    const double* vp = vbuf[cur];
-    const double* wp = wbuf[cur];
-    double ks = 0.0;
-    for (int w = 0; w < kTriThreads / 64; ++w) ks += redK[w];
-    const double K = kscale * ks;
-    const int a = n - 2, b = n - 1;
-    const double wa = fma(-K, vp[a], wp[a]), wb = fma(-K, vp[b], wp[b]);
-    const bool lds = k0 <= a;
-    const double aa = lds ? T[tri_off(a, a, k0)] : W[(int64_t)a * kBigPitch + a];
-    const double bb = lds ? T[tri_off(b, b, k0)] : W[(int64_t)b * kBigPitch + b];
-    const double ba = lds ? T[tri_off(b, a, k0)] : W[(int64_t)b * kBigPitch + a];
-    dg[a] = aa - 2.0 * vp[a] * wa;
-    dg[b] = bb - 2.0 * vp[b] * wb;
-    eg[a] = ba - vp[b] * wa - wb * vp[a];
-    tg[a] = 0.0;
-    tg[b] = 0.0;
-  }
-}
-
-// Static LDS of k_tridiag_big (vectors, sums, scalars) and its first LDS step: the smallest
-// k0 whose trailing lower triangle (n - k0 rows) fits in the rest of the LDS.
-constexpr size_t kTriStaticBytes = (5 * kBigPitch + 2 * (kTriThreads / 64) + 3) * sizeof(double);
-static void tri_lds_plan(int n, int* k0, size_t* bytes) {
-  const size_t budget = (kLdsBytes - kTriStaticBytes - 256) / sizeof(double);
-  int m0 = n;
-  while (m0 > 0 && (size_t)m0 * (m0 + 1) / 2 > budget) --m0;
-  *k0 = n - m0;
-  *bytes = (size_t)m0 * (m0 + 1) / 2 * sizeof(double);
-}
-
-// Steps 2-3 on the tridiagonal form of k_tridiag_big (one work-group of kTopThreads): the
-// eigenvectors of T go to vecs, k_back_wy applies the reflectors.
-template <int RMAX>
-__global__ __launch_bounds__(kTopThreads) void k_eig_top_big(const double* __restrict__ W, int n, int r,
-                                                             double* __restrict__ vecs, double* __restrict__ vals,
-                                                             int bv, int gl) {
-  constexpr int NB = kBigPitch / 16;
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double dd[kBigPitch], ee[kBigPitch], e2[kBigPitch], taus[kBigPitch];
-  __shared__ double lam[kTopMaxR], rdiag[kTopMaxR], colx[2][64];
-  __shared__ int twist[kTopMaxR];
-  const int tid = threadIdx.x;
-  const int rp = r + 1;
-  double* Ys = reinterpret_cast<double*>(smem);  // n x rp eigenvectors of T, then of A
-  double* Gm = Ys + n * rp;                      // r x rp Gram / R factor
-  double* Xi = Gm + r * rp;                      // 1 / R_jj
-  double* SD = Xi + r * rp;                      // twisted factorisations, [i * bv + t]
-  double* SL = SD + n * bv;
-  double* SU = SL + n * bv;
-  const double* dg = W + (int64_t)n * kBigPitch;
-  for (int i = tid; i < kBigPitch; i += kTopThreads) {
-    dd[i] = i < n ? dg[i] : 0.0;
-    ee[i] = i + 1 < n ? dg[kBigPitch + i] : 0.0;
-    taus[i] = i < n ? dg[2 * kBigPitch + i] : 0.0;
-  }
-  __syncthreads();
-  eig_top_tail<NB, RMAX, false>(n, r, bv, gl, dd, ee, e2, taus, ReflPitched{W}, lam, rdiag, colx, twist, Ys, Gm, Xi,
-                                SD, SL, SU, vecs, vals);
-}
-
-// ----------------------------------------------------------------------------------
-// Step 4 for k_tridiag_big's reflectors: vecs (n x r, row pitch n) <- Q vecs with
-// Q = H_0 H_1 ... H_{n-3}, in compact-WY panels of kWyPanel reflectors applied last panel
-// first.  Panel p (reflectors k0 = 16 p ...) is P = I - V T V^T with T upper triangular:
-// T_jj = tau_j and column j above the diagonal -tau_j T (V_{<j}^T v_j).  The T factors of
-// all panels are formed first (one wave each, row a of T in lane a), then each panel is
-// three small products over Y held in LDS: X = V^T Y, X <- T X, Y <- Y - V X.  One
-// work-group of 1024 threads.
-// ----------------------------------------------------------------------------------
-constexpr int kWyPanel = 16;
-constexpr int kWyThreads = 1024;
-constexpr int kWyPairs = kWyPanel * (kWyPanel - 1) / 2;
-
-template <int RMAX>
-__global__ __launch_bounds__(kWyThreads) void k_back_wy(const double* __restrict__ W, int n, int r,
-                                                        double* __restrict__ vecs) {
-  constexpr int P = kWyPanel;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int rp = r + 1;
-  const int npan = (n - 3) / P + 1;  // reflectors 0 .. n - 3
-  double* Ys = reinterpret_cast<double*>(smem);  // n x rp
-  double* Vp = Ys + n * rp;                      // n x (P + 1): the current panel, zero where v is
-  double* Ts = Vp + n * (P + 1);                 // npan x P x P
-  double* Gs = Ts + npan * P * P;                // npan x kWyPairs: v_a . v_b, a < b
-  double* Xs = Gs + npan * kWyPairs;             // P x rp
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const double* taus = W + (int64_t)(n + 2) * kBigPitch;
-  for (int e = tid; e < n * r; e += kWyThreads) Ys[(e / r) * rp + e % r] = vecs[(e / r) * n + e % r];
-  // Gram entries of every panel: v_{k0+a} . v_{k0+b} over rows i > k0 + b
-  for (int e = tid; e < npan * kWyPairs; e += kWyThreads) {
-    const int pn = e / kWyPairs;
-    int q = e - pn * kWyPairs, b = 1;
-    while (q >= b) { q -= b; ++b; }  // pair (a = q, b), a < b
-    const int ka = pn * P + q, kb = pn * P + b;
-    double g = 0.0;
-    if (kb <= n - 3)
-      for (int i = kb + 1; i < n; ++i) g = fma(W[(int64_t)ka * kBigPitch + i], W[(int64_t)kb * kBigPitch + i], g);
-    Gs[e] = g;
-  }
-  __syncthreads();
-  if (wid < npan && lane < P) {
-    // row a = lane of T for panel wid: T_aj = -tau_j sum_{b=a}^{j-1} T_ab G_bj (j > a)
-    const int k0 = wid * P, a = lane;
-    const double* G = Gs + wid * kWyPairs;
-    double trow[P];
-#pragma unroll
-    for (int j = 0; j < P; ++j) {
-      const double tj = k0 + j <= n - 3 ? taus[k0 + j] : 0.0;
-      double v = 0.0;
-      if (j == a) {
-        v = tj;
-      } else if (j > a) {
-        double acc = 0.0;
-#pragma unroll
-        for (int b = 0; b < j; ++b)
-          if (b >= a) acc = fma(trow[b], G[j * (j - 1) / 2 + b], acc);
-        v = -tj * acc;
-      }
-      trow[j] = v;
-    }
-#pragma unroll
-    for (int j = 0; j < P; ++j) Ts[(wid * P + a) * P + j] = trow[j];
-  }
-  for (int pn = npan - 1; pn >= 0; --pn) {
-    const int k0 = pn * P;
-    const int kc = min(P, n - 2 - k0);  // reflectors of this panel
-    __syncthreads();
-    for (int e = tid; e < n * P; e += kWyThreads) {
-      const int i = e / P, j = e % P;
-      const int k = k0 + j;
-      Vp[i * (P + 1) + j] = (j < kc && i > k) ? W[(int64_t)k * kBigPitch + i] : 0.0;
-    }
-    __syncthreads();
-    {  // X = V^T Y: two lanes per entry (alternate rows), summed by one lane exchange
-      const int ent = tid >> 1, h = tid & 1;
-      const int j = ent / RMAX, c = ent % RMAX;
-      double acc = 0.0;
-      if (j < kc && c < r)
-        for (int i = k0 + 1 + j + h; i < n; i += 2) acc = fma(Vp[i * (P + 1) + j], Ys[i * rp + c], acc);
-      acc += dpp_mov<0xB1>(acc);
-      if (h == 0 && j < P && c < r) Xs[j * rp + c] = acc;
-    }
-    __syncthreads();
-    double x2 = 0.0;
-    const int j2 = tid / RMAX, c2 = tid % RMAX;
-    if (j2 < kc && c2 < r) {
-      const double* T = Ts + (pn * P + j2) * P;
-      for (int b = j2; b < kc; ++b) x2 = fma(T[b], Xs[b * rp + c2], x2);
-    }
-    __syncthreads();
-    if (j2 < P && c2 < r) Xs[j2 * rp + c2] = x2;
-    __syncthreads();
-    for (int e = tid; e < (n - k0 - 1) * r; e += kWyThreads) {
-      const int i = k0 + 1 + e / r, c = e % r;
-      double acc = Ys[i * rp + c];
-#pragma unroll
-      for (int j = 0; j < P; ++j) acc = fma(-Vp[i * (P + 1) + j], Xs[j * rp + c], acc);
-      Ys[i * rp + c] = acc;
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < n * r; e += kWyThreads) vecs[(e / r) * n + e % r] = Ys[(e / r) * rp + e % r];
-}
-
-static size_t back_wy_lds(int n, int r) {
-  const int npan = (n - 3) / kWyPanel + 1;
-  return ((size_t)n * (r + 1) + (size_t)n * (kWyPanel + 1) + (size_t)npan * kWyPanel * kWyPanel +
-          (size_t)npan * kWyPairs + (size_t)kWyPanel * (r + 1)) * sizeof(double);
-}
-
-// Dynamic LDS of k_eig_top_big: Y, its Gram / R factor and 1 / R_jj, bv twisted factorisations.
-static size_t eig_top_big_lds(int n, int r, int bv) {
-  return ((size_t)n * (r + 1) + 2 * (size_t)r * (r + 1)) * 8 + (size_t)bv * n * 24 + 16;
-}
-
-template <int RMAX>
-static hipError_t launch_eig_top_big(const double* a, int n, int r, double* vecs, double* vals, double* work,
-                                     hipStream_t st, int bv) {
-  int k0 = 0;
-  size_t tri_bytes = 0;
-  tri_lds_plan(n, &k0, &tri_bytes);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_tridiag_big),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)tri_bytes);
-  if (e != hipSuccess) { (void)hipGetLastError(); return e; }
-  hipLaunchKernelGGL(k_tridiag_big, dim3(1), dim3(kTriThreads), tri_bytes, st, a, n, work, k0);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const size_t lds = eig_top_big_lds(n, r, bv);
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_eig_top_big<RMAX>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) { (void)hipGetLastError(); return e; }
-  int gl = 16;
-  while (gl > 2 && (kTopThreads / 64) * (64 / gl) < r) --gl;
-  hipLaunchKernelGGL((k_eig_top_big<RMAX>), dim3(1), dim3(kTopThreads), lds, st, work, n, r, vecs, vals, bv, gl);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const size_t wy = back_wy_lds(n, r);
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_back_wy<RMAX>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)wy);
-  if (e != hipSuccess) { (void)hipGetLastError(); return e; }
-  hipLaunchKernelGGL((k_back_wy<RMAX>), dim3(1), dim3(kWyThreads), wy, st, work, n, r, vecs);
-  return hipGetLastError();
-}
-
-hipError_t sym_eig_top(const double* a, int n, int r, double* vecs, double* vals, double* work, hipStream_t st) {
-  if (n <= 0 || r <= 0) return hipErrorInvalidValue;
-  if (r > n) r = n;
-  // largest batch of twisted factorisations that fits next to the static arrays (~12 KB)
-  const size_t budget = kLdsBytes - 14 * 1024;
-  int bv = r < kTopThreads / 2 ? r : kTopThreads / 2;
-  while (bv > 1 && eig_top_lds(n, r, bv) > budget) --bv;
-  if (n > kTopMaxN && n <= kBigPitch && r <= 32 && work) {
-    // static arrays of k_eig_top_big: about 11 KB
-    const size_t big_budget = kLdsBytes - 14 * 1024;
-    int bvb = r < kTopThreads / 2 ? r : kTopThreads / 2;
-    while (bvb > 1 && eig_top_big_lds(n, r, bvb) > big_budget) --bvb;
-    if (eig_top_big_lds(n, r, bvb) <= big_budget) {
-      if (r <= 16) return launch_eig_top_big<16>(a, n, r, vecs, vals, work, st, bvb);
-      return launch_eig_top_big<32>(a, n, r, vecs, vals, work, st, bvb);
-    }
-  }
-  if (n > kTopMaxN || r > kTopMaxR || eig_top_lds(n, r, bv) > budget) {
-    const hipError_t e = sym_eig(a, n, vecs, vals, work, st);
-    if (e != hipSuccess || r == n) return e;
-    return axpby(1, n - r, 0.0, nullptr, 0, 0.0, vals + r, n, nullptr, st);  // vals[r..n) = 0
-  }
-  switch ((n + 15) / 16) {
-    case 1: return launch_eig_top<1>(a, n, r, vecs, vals, st, bv);
-    case 2: return launch_eig_top<2>(a, n, r, vecs, vals, st, bv);
-    case 3: return launch_eig_top<3>(a, n, r, vecs, vals, st, bv);
-    case 4: return launch_eig_top<4>(a, n, r, vecs, vals, st, bv);
-    case 5: return launch_eig_top<5>(a, n, r, vecs, vals, st, bv);
-    case 6: return launch_eig_top<6>(a, n, r, vecs, vals, st, bv);
-    case 7: return launch_eig_top<7>(a, n, r, vecs, vals, st, bv);
-    default: return launch_eig_top<8>(a, n, r, vecs, vals, st, bv);
-  }
-}
-
-// ----------------------------------------------------------------------------------
 // SVQB transform, Ritz / saturated selection.
 // ----------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_svqb(const double* __restrict__ vecs, const double* __restrict__ vals, int n,
@@ -2114,115 +925,6 @@ __global__ __launch_bounds__(256) void k_identity(double* __restrict__ a, int64_
 
 hipError_t identity(double* a, int64_t m, hipStream_t st) {
   hipLaunchKernelGGL(k_identity, dim3((unsigned)((m * m + 255) / 256)), dim3(256), 0, st, a, m);
-  return hipGetLastError();
-}
-
-// ----------------------------------------------------------------------------------
-// TT reconstruction error.  The modes are split at s: the right part
-// R (r_s x inner) = contraction of cores s+1..d is formed once (by the caller);
-// work-group o (one outer index tuple of modes 1..s) forms its left interface row
-// L = G_1[i_1] ... G_s[i_s] (1 x r_s) and the inner slab Xhat = L R, and
-// accumulates ||X - Xhat||^2, ||X||^2 and max |Xhat| in float64.
-// ----------------------------------------------------------------------------------
-struct TTErrArgs {
-  int s;
-  int64_t dims[TTR_MAX_D];
-  int64_t ranks[TTR_MAX_D + 1];
-  const double* cores[TTR_MAX_D];
-};
-
-template <typename TX>
-__global__ __launch_bounds__(256) void k_tt_error(const TX* __restrict__ x, int64_t outer, int64_t inner,
-                                                  TTErrArgs args, const double* __restrict__ R,
-                                                  double* __restrict__ part) {
-  __shared__ double L[2][64];
-  __shared__ double red[256];
-  const int tid = threadIdx.x;
-  const int64_t o = blockIdx.x;
-  // digits of o in the mixed radix dims[0..s-1] (first index slowest)
-  int64_t idx[TTR_MAX_D];
-  int64_t rem = o;
-  for (int k = args.s - 1; k >= 0; --k) { idx[k] = rem % args.dims[k]; rem /= args.dims[k]; }
-  if (tid < 64) L[0][tid] = tid == 0 ? 1.0 : 0.0;
-  __syncthreads();
-  int cur = 0;
-  for (int k = 0; k < args.s; ++k) {
-    const int64_t ra = args.ranks[k], rb = args.ranks[k + 1], I = args.dims[k];
-    const double* Gk = args.cores[k];
-    if (tid < rb) {
-      double acc = 0.0;
-      for (int a = 0; a < ra; ++a) acc += L[cur][a] * Gk[((int64_t)a * I + idx[k]) * rb + tid];
-      L[cur ^ 1][tid] = acc;
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-  const int rs = (int)args.ranks[args.s];
-  double e2 = 0.0, x2 = 0.0, xinf = 0.0;
-  const TX* xo = x + o * inner;
-  for (int64_t e = tid; e < inner; e += 256) {
-    double xh = 0.0;
-    for (int a = 0; a < rs; ++a) xh += L[cur][a] * R[(int64_t)a * inner + e];
-    const double xv = (double)xo[e];
-    const double df = xv - xh;
-    e2 += df * df;
-    x2 += xv * xv;
-    xinf = fmax(xinf, fabs(xh));
-  }
-  const double se2 = block_sum(e2, red);
-  const double sx2 = block_sum(x2, red);
-  red[tid] = xinf;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) red[tid] = fmax(red[tid], red[tid + off]);
-    __syncthreads();
-  }
-  if (tid == 0) {
-    part[o * 3 + 0] = se2;
-    part[o * 3 + 1] = sx2;
-    part[o * 3 + 2] = red[0];
-  }
-}
-
-__global__ __launch_bounds__(256) void k_tt_error_finish(const double* __restrict__ part, int64_t outer,
-                                                         double* __restrict__ out3) {
-  __shared__ double r0[256], r1[256], r2[256];
-  const int tid = threadIdx.x;
-  // fixed assignment of outer blocks to threads, then a fixed tree
-  const int64_t per = (outer + 255) / 256;
-  double a = 0.0, b = 0.0, c = 0.0;
-  for (int64_t o = tid * per; o < (tid + 1) * per && o < outer; ++o) {
-    a += part[o * 3]; b += part[o * 3 + 1]; c = fmax(c, part[o * 3 + 2]);
-  }
-  r0[tid] = a; r1[tid] = b; r2[tid] = c;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) { r0[tid] += r0[tid + off]; r1[tid] += r1[tid + off]; r2[tid] = fmax(r2[tid], r2[tid + off]); }
-    __syncthreads();
-  }
-  if (tid == 0) { out3[0] = r0[0]; out3[1] = r1[0]; out3[2] = r2[0]; }
-}
-
-hipError_t tt_error_blocks(const void* x, int xdt, int64_t outer, int64_t inner, int s_split, const int64_t* dims,
-                           const int64_t* ranks, const double* const* cores, const double* R, double* part,
-                           double* out3, hipStream_t st) {
-  TTErrArgs args;
-  args.s = s_split;
-  for (int k = 0; k < TTR_MAX_D; ++k) {
-    args.dims[k] = k < s_split ? dims[k] : 1;
-    args.cores[k] = k < s_split ? cores[k] : nullptr;
-  }
-  for (int k = 0; k <= TTR_MAX_D; ++k) args.ranks[k] = k <= s_split ? ranks[k] : 1;
-  const dim3 grid((unsigned)outer);
-  if (xdt == TTR_F64)
-    hipLaunchKernelGGL(k_tt_error<double>, grid, dim3(256), 0, st, (const double*)x, outer, inner, args, R, part);
-  else if (xdt == TTR_F32)
-    hipLaunchKernelGGL(k_tt_error<float>, grid, dim3(256), 0, st, (const float*)x, outer, inner, args, R, part);
-  else
-    hipLaunchKernelGGL(k_tt_error<__bf16>, grid, dim3(256), 0, st, (const __bf16*)x, outer, inner, args, R, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tt_error_finish, dim3(1), dim3(256), 0, st, part, outer, out3);
   return hipGetLastError();
 }
 

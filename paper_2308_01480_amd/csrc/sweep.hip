@@ -488,7 +488,10 @@ hipError_t tt_error_run(const void* x, int x_dtype, int d, const int64_t* dims, 
     R = out;
     which ^= 1;
   }
-  return tt_error_blocks(x, x_dtype, outer, inner, s, dims, ranks, cores, R, part, out3, st);
+  // partial sums: the buffer that does not hold R, or the outer triples when there are more
+  int64_t groups = outer;
+  if (rmax * inner / 3 > outer) { part = buf[which]; groups = rmax * inner / 3; }
+  return tt_error_blocks(x, x_dtype, outer, inner, s, dims, ranks, cores, R, part, groups, out3, st);
 }
 
 }  // namespace ttr
