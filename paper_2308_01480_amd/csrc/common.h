@@ -27,9 +27,9 @@ constexpr size_t kLdsBytes = 160 * 1024;  // LDS per CU on gfx950
 constexpr int kMaxSmall = 256;            // largest Gram / Rayleigh-Ritz eigenproblem
 constexpr int kRowChunk = 256;            // row chunk of the A^T Z kernel
 constexpr int kSplitTCols = 128;         // tile columns of the split-operand float32 A^T Z kernel
-// Block orthonormalisation: at most kOrthMaxGroups row work-groups whose last one sums
-// the partials, or, for tall blocks (more 64-row chunks than that), up to kOrthBigGroups
-// row work-groups followed by a separate reduction launch.
+// Block orthonormalisation: at most kOrthMaxGroups row work-groups whose partials the next
+// launch sums itself, or, for tall blocks (more 64-row chunks than that), up to
+// kOrthBigGroups row work-groups followed by a separate summing launch.
 constexpr int kOrthMaxGroups = 15;
 constexpr int kOrthBigGroups = 256;
 inline bool orth_big_rows(int64_t m) { return (m + 63) / 64 > kOrthMaxGroups; }
@@ -193,7 +193,7 @@ struct Layout {
   size_t small;        // small float64 matrices (Gram, eigenvectors, transforms)
   size_t small_bytes;
   size_t orth_big;     // partials of the tall-block orthonormalisation (0 bytes if unused):
-  size_t orth_big_bytes;  // kOrthBigGroups x w s, then kOrthBigGroups norms, then 64 x 64 (gsum)
+  size_t orth_big_bytes;  // kOrthBigGroups x w s, then kOrthBigGroups norms
   int small_ne;         // side of the square float64 matrices carved from `small`
   size_t total;
 };

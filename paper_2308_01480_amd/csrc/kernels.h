@@ -82,43 +82,39 @@ hipError_t launch_gram_bf16(const StreamArgs& a, double* gm);
 hipError_t launch_aw_split(const StreamArgs& a, bool omega = false);
 hipError_t launch_atz_split(const StreamArgs& a, void* out, int64_t ldo, int s_out, int outmode);
 
-// Block orthonormalisation in row-parallel launches (block_orth.hip).  G <= kOrthMaxGroups
-// work-groups write partials (G x len doubles in `part`, G doubles in `norm_part`); the
-// last one, found through `counter` (zero between launches), reduces them.
+// Block orthonormalisation in row-parallel launches (block_orth.hip).
 struct OrthArgs {
   int64_t m = 0;
   int s = 0, js = 0;                               // block width, previous basis width
   const double* Q = nullptr; int64_t ldq = 0;      // previous basis (m x js)
-  double* P = nullptr; int64_t ldp = 0;            // projected block (m x s)
+  double* P = nullptr; int64_t ldp = 0;            // once projected block (m x s; js > 0)
   double* U = nullptr; int64_t ldu = 0;            // P T1 (m x s)
-  double* h = nullptr; double* h2 = nullptr;       // js x s projection coefficients
-  double* T1 = nullptr; double* T2 = nullptr;      // s x s transforms of the two passes
+  double* T1 = nullptr;                            // first transform (s x s; only with Tprod)
   double* Tprod = nullptr;                         // T1 T2 (optional)
   int* kept1 = nullptr; int* kept2 = nullptr;
   double* ref = nullptr;                           // ||Y||_F^2 of the raw block
-  bool ref_from_gram = false;                      // ref = trace(P^T P) of the first update
+  bool ref_from_gram = false;                      // ref = trace(Y^T Y), written (js = 0)
   double coef = 0.0;                               // first-pass drop: pivot <= coef * ref
   double thresh2 = 1e-6;                           // second-pass drop threshold
-  double* part = nullptr; size_t part_bytes = 0;
-  double* norm_part = nullptr;
-  int* counter = nullptr;
+  double* part = nullptr; size_t part_bytes = 0;   // partials of the row groups
+  double* norm_part = nullptr; int norm_cap = 0;   // partial norms (js > 0): at most norm_cap groups
+  bool big = false;                                // tall block: up to kOrthBigGroups groups
+  bool two_parts = false;                          // set by orth_step: part holds two buffers
+  // sums of separate summing launches (tall blocks, sums that do not fit in LDS): h and h2
+  // (js x s), the Grams (s x s)
+  double* h = nullptr; double* h2 = nullptr; double* gsum = nullptr;
   double* Qout = nullptr; int64_t ldqo = 0;        // Q_j (m x s)
   void* zs = nullptr; int zdt = 0; int64_t m_pad = 0; int Sz = 0;  // stream copy of Q_j
+  int* status = nullptr;                           // set to 1 when Y holds a non-finite entry
   hipStream_t st = nullptr;
-  // Tall blocks: up to kOrthBigGroups row-parallel work-groups write partials (part,
-  // norm_part sized for them), and a separate reduction launch sums them in group order;
-  // its last work-group runs the s x s step on the sum, kept in gsum (s x s).
-  bool big = false;
-  double* gsum = nullptr;
 };
 
-hipError_t orth_reset_counter(int* counter, hipStream_t st);  // *counter = 0 (device)
+// Q_j (a.Qout), kept counts and the stream copy from the raw block Y (m x s, ldy): projected
+// twice against a.Q, then the two passes of the rank-revealing QR.
+hipError_t orth_step(const OrthArgs& a, const double* Y, int64_t ldy);
+hipError_t zero_int(int* p, hipStream_t st);  // *p = 0 (device)
 // *status = 1 when any of v[0..n) is not finite (status otherwise left unchanged)
 hipError_t flag_nonfinite(const double* v, int64_t n, int* status, hipStream_t st);
-hipError_t orth_project(const OrthArgs& a, const double* Y, int64_t ldy);     // h = Q^T Y (+ ref)
-hipError_t orth_update(const OrthArgs& a, const double* S, int64_t lds, const double* W, bool next_proj);
-hipError_t orth_tgram(const OrthArgs& a);                                     // U = P T1, T2
-hipError_t orth_out(const OrthArgs& a);                                       // Q_j = U T2
 
 // Small dense float64 kernels (small_kernels.hip).
 // C (ka x kb, ldc) = alpha * X^T Y + beta * C, X: m x ka (ldx, dtype xdt), Y: m x kb (ldy, ydt).
@@ -147,14 +143,6 @@ hipError_t sym_eig_top(const double* a, int n, int r, double* vecs, double* vals
 // vals[j] > thresh, the rest zero.  thresh = coef * (*ref) (ref on device; NULL: vals[0]).
 hipError_t svqb_transform(const double* vecs, const double* vals, int n, const double* ref, double coef,
                           double* T, int* kept, hipStream_t st);
-// Rank-revealing first pass: T (s x s) from the pivoted Cholesky of Gm = P^T P (the R of
-// P's column-pivoted QR), pivots d > coef * (*ref) kept; P T = leading columns of Q.
-hipError_t qrcp_transform(const double* Gm, int s, const double* ref, double coef, double* T, int* kept,
-                          hipStream_t st);
-// Second-pass transform T = R^{-1} of the Cholesky factor of Gm (s x s, s <= 64) restricted to
-// the first *kept_in columns, dropping pivots <= thresh; surviving columns packed first.
-hipError_t chol_inv_transform(const double* Gm, int s, const int* kept_in, double thresh, double* T, int* kept_out,
-                              hipStream_t st);
 // Saturated selection: G (m x r) = eigenvectors j < r with vals[j] > tau^2 * sum_{i<r} vals[i]; nv = count.
 hipError_t sat_select(const double* vecs, const double* vals, int m, int r, double tau, double* G, int* nv,
                       hipStream_t st);

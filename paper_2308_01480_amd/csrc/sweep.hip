@@ -41,12 +41,10 @@ struct SmallBufs {
   int* ints;      // kept counts
   size_t splitk_bytes = 0;     // bytes of splitk (also the block orthonormalisation partials)
   double* norm_part = nullptr; // kOrthMaxGroups partial norms
-  int* counter = nullptr;      // last-work-group counter of the block orthonormalisation
-  // tall blocks: partials of up to kOrthBigGroups row work-groups, their norms, the s x s sum
+  // tall blocks: partials of up to kOrthBigGroups row work-groups and their norms
   double* big_part = nullptr;
   size_t big_part_bytes = 0;
   double* big_norm = nullptr;
-  double* big_gsum = nullptr;
 };
 
 static SmallBufs carve_small(char* base, size_t bytes, int ne) {
@@ -64,7 +62,6 @@ static SmallBufs carve_small(char* base, size_t bytes, int ne) {
   b.ints = reinterpret_cast<int*>(p); p += 512;
   b.splitk_bytes = 15 * sq * sizeof(double);
   b.norm_part = b.scal + 448;
-  b.counter = b.ints + 1023;
   (void)bytes;
   return b;
 }
@@ -90,41 +87,31 @@ struct ModeCtx {
   bool* fused_next = nullptr;      // set when this mode's carry also formed mode k + 1's Y0
 };
 
-// Rank-revealing orthonormal basis of P (m x s), the economy QR of Algorithm 3
-// step 5 with column pivoting: the block Gram's pivoted Cholesky keeps the leading
-// pivots with |R_jj|^2 > coef * (*ref) and gives Q1 = P R_11^{-1} (scattered), then a
-// Cholesky QR pass restores the orthogonality lost to the Gram's squared
-// conditioning.  Q (ld ldq) gets the kept columns first, zeros after; *kept2 is
-// their number.  Uses `tmp` (m x s) as the intermediate basis.
 // Common fields of the block orthonormalisation launches.
 static OrthArgs orth_args(int64_t m, int s, double coef, const SmallBufs& sb, hipStream_t st) {
   OrthArgs a;
   a.m = m; a.s = s; a.coef = coef; a.thresh2 = 1e-6;
-  a.part = sb.splitk; a.part_bytes = sb.splitk_bytes; a.norm_part = sb.norm_part; a.counter = sb.counter;
+  a.part = sb.splitk; a.part_bytes = sb.splitk_bytes; a.norm_part = sb.norm_part; a.norm_cap = kOrthMaxGroups;
   if (orth_big_rows(m) && sb.big_part) {
+    a.part = sb.big_part; a.part_bytes = sb.big_part_bytes; a.norm_part = sb.big_norm; a.norm_cap = kOrthBigGroups;
     a.big = true;
-    a.part = sb.big_part; a.part_bytes = sb.big_part_bytes; a.norm_part = sb.big_norm; a.gsum = sb.big_gsum;
   }
-  a.h = sb.vecs; a.h2 = sb.gram; a.T1 = sb.tmat; a.T2 = sb.hmat;
+  a.h = sb.vecs; a.h2 = sb.gram; a.gsum = sb.hmat; a.T1 = sb.tmat;
   a.st = st;
   return a;
 }
 
 // Rank-revealing orthonormal basis Q (ld ldq) of the m x s block Src (ld s), with drops
-// relative to *ref: the pivoted Cholesky of P^T P (first pass) then a Cholesky-QR pass;
-// P (m x s) receives a copy of Src (may be Src itself), tmp the first-pass basis, and
-// tprod = T1 T2 when given.
+// relative to *ref: the pivoted Cholesky of Src^T Src (first pass) then a Cholesky-QR pass;
+// tmp (m x s) receives the first-pass basis, and tprod = T1 T2 when given.
 // ref_from_gram: *ref is written with ||Src||_F^2 (the trace of the block Gram) before use.
-static int orth_block(const double* Src, double* P, int64_t m, int s, double* ref, double coef, double* Q, int64_t ldq,
-                      double* tmp, int* kept1, int* kept2, const SmallBufs& sb, hipStream_t st,
-                      double* tprod = nullptr, bool ref_from_gram = false) {
+static int orth_block(const double* Src, int64_t m, int s, double* ref, double coef, double* Q, int64_t ldq, double* tmp,
+                      int* kept1, int* kept2, const SmallBufs& sb, hipStream_t st, double* tprod, bool ref_from_gram) {
   OrthArgs a = orth_args(m, s, coef, sb, st);
-  a.P = P; a.ldp = s; a.U = tmp; a.ldu = s; a.ref = ref; a.kept1 = kept1; a.kept2 = kept2; a.Tprod = tprod;
+  a.U = tmp; a.ldu = s; a.ref = ref; a.kept1 = kept1; a.kept2 = kept2; a.Tprod = tprod;
   a.ref_from_gram = ref_from_gram;
   a.Qout = Q; a.ldqo = ldq;
-  TTR_CHECK(orth_update(a, Src, s, nullptr, false));
-  TTR_CHECK(orth_tgram(a));
-  TTR_CHECK(orth_out(a));
+  TTR_CHECK(orth_step(a, Src, s));
   return TTR_OK;
 }
 
@@ -235,19 +222,18 @@ static int run_regular(const ModeCtx& c) {
   } else if (!c.sketch_ready) {
     TTR_CHECK(sketch_pass(sa, c.seed, g.k, S, wbuf));
   }  // else Y0 was formed in pbuf by the previous mode's carry pass
-  // every entry of A reaches Y0 through a dense Omega row: a NaN or infinity in A (or an
-  // overflow of the products) leaves a non-finite entry here
-  TTR_CHECK(flag_nonfinite(pbuf, m * s, c.status, c.st));
   OrthArgs oa = orth_args(m, s, coef, sb, c.st);
   oa.Q = qbuf; oa.ldq = w; oa.P = pbuf; oa.ldp = s; oa.U = ybuf; oa.ldu = s;
+  // every entry of A reaches Y0 through a dense Omega row: a NaN or infinity in A (or an
+  // overflow of the products) leaves a non-finite entry there
+  oa.status = c.status;
   oa.zs = zs; oa.zdt = c.adt; oa.m_pad = g.m_pad; oa.Sz = S;
   oa.js = 0; oa.ref = sb.scal + 0; oa.ref_from_gram = true;
   oa.kept1 = sb.ints + 0; oa.kept2 = kept ? kept : sb.ints + 1;
   oa.Tprod = c.tape ? c.tape->T : nullptr;
   oa.Qout = qbuf; oa.ldqo = w;
-  TTR_CHECK(orth_update(oa, pbuf, s, nullptr, false));
-  TTR_CHECK(orth_tgram(oa));
-  TTR_CHECK(orth_out(oa));
+  TTR_CHECK(orth_step(oa, pbuf, s));
+  oa.status = nullptr;
 
   // Krylov blocks Y_j = A A^T Q_{j-1}, j = 1..q+1 (the last one only feeds Rayleigh-Ritz).
   for (int j = 1; j <= q + 1; ++j) {
@@ -269,11 +255,7 @@ static int run_regular(const ModeCtx& c) {
     oa.kept1 = sb.ints + 2 * j; oa.kept2 = kept ? kept + j : sb.ints + 2 * j + 1;
     oa.Tprod = c.tape ? c.tape->T + (size_t)j * s * s : nullptr;
     oa.Qout = qbuf + j * s;
-    TTR_CHECK(orth_project(oa, yj, w));
-    TTR_CHECK(orth_update(oa, yj, w, oa.h, true));
-    TTR_CHECK(orth_update(oa, pbuf, s, oa.h2, false));
-    TTR_CHECK(orth_tgram(oa));
-    TTR_CHECK(orth_out(oa));
+    TTR_CHECK(orth_step(oa, yj, w));
   }
 
   // Rayleigh-Ritz: M = Q^T A A^T Q = Q^T [Y_1 .. Y_{q+1}], top-r eigenvectors, G = Q U.
@@ -316,9 +298,8 @@ static int run_power(const ModeCtx& c) {
 
   sa.y = pbuf; sa.ldy = b;
   TTR_CHECK(sketch_pass(sa, c.seed, g.k, B, wbuf));
-  TTR_CHECK(flag_nonfinite(pbuf, m * b, c.status, c.st));
   OrthArgs oa = orth_args(m, b, c.tau * c.tau, sb, c.st);
-  oa.Q = qbuf; oa.ldq = b; oa.P = pbuf; oa.ldp = b; oa.U = ybuf; oa.ldu = b;
+  oa.U = ybuf; oa.ldu = b;
   oa.zs = zs; oa.zdt = c.adt; oa.m_pad = g.m_pad; oa.Sz = B;
   oa.js = 0; oa.ref = sb.scal + 0; oa.ref_from_gram = true;
   oa.kept1 = sb.ints + 0; oa.kept2 = sb.ints + 1;
@@ -338,9 +319,8 @@ static int run_power(const ModeCtx& c) {
     const bool last = it == g.iters;
     oa.Qout = (last && last_is_core) ? c.core : qbuf;
     oa.ldqo = b;
-    TTR_CHECK(orth_update(oa, it == 0 ? pbuf : yall, b, nullptr, false));
-    TTR_CHECK(orth_tgram(oa));
-    TTR_CHECK(orth_out(oa));
+    oa.status = it == 0 ? c.status : nullptr;
+    TTR_CHECK(orth_step(oa, it == 0 ? pbuf : yall, b));
   }
   if (!last_is_core) {
     // Rayleigh-Ritz on span(Q): M = Q^T A A^T Q, top-r eigenvectors, G = Q U
@@ -388,7 +368,7 @@ static int run_saturated(const ModeCtx& c) {
   TTR_CHECK(flag_nonfinite(sb.gram, (int64_t)n * n, c.status, c.st));  // A^T A sees every entry of A
   TTR_CHECK(eigen(c, sb.gram, n, g.r, evec, eval));
   TTR_CHECK(gemm_nn(g.m, n, g.r, c.A, c.adt, n, evec, n, 1.0, 0.0, pbuf, g.r, c.st));
-  int rc = orth_block(pbuf, pbuf, g.m, g.r, sb.scal + 400, c.tau * c.tau, c.core, g.r, ybuf, sb.ints + 1021, nv, sb, c.st,
+  int rc = orth_block(pbuf, g.m, g.r, sb.scal + 400, c.tau * c.tau, c.core, g.r, ybuf, sb.ints + 1021, nv, sb, c.st,
                       c.tape ? c.tape->T : nullptr, true);
   if (rc) return rc;
   TTR_CHECK(complete_columns(c.core, g.m, g.r, nv, ybuf, c.st));
@@ -410,16 +390,13 @@ int sweep(const void* x, const Plan& pl, uint64_t seed, double* const* cores, ch
   const int d = P.d;
   SmallBufs sb = carve_small(ws + pl.lay.small, pl.lay.small_bytes, pl.lay.small_ne);
   if (pl.lay.orth_big_bytes) {
-    // kOrthBigGroups partials of the longest step, then the groups' norms, then the s x s sum
-    const size_t gsum_bytes = (size_t)64 * 64 * 8, norm_bytes = (size_t)kOrthBigGroups * 8;
+    // kOrthBigGroups partials of the longest step, then the groups' norms
     sb.big_part = reinterpret_cast<double*>(ws + pl.lay.orth_big);
-    sb.big_part_bytes = pl.lay.orth_big_bytes - gsum_bytes - norm_bytes;
+    sb.big_part_bytes = pl.lay.orth_big_bytes - (size_t)kOrthBigGroups * 8;
     sb.big_norm = sb.big_part + sb.big_part_bytes / 8;
-    sb.big_gsum = sb.big_norm + kOrthBigGroups;
   }
   int* status = reinterpret_cast<int*>(ws + kStatusOffset);
-  TTR_CHECK(orth_reset_counter(sb.counter, st));
-  TTR_CHECK(orth_reset_counter(status, st));
+  TTR_CHECK(zero_int(status, st));
   const void* A = x;
   int adt = P.x_dtype;
   int ping = 0;
@@ -746,21 +723,21 @@ int ttr_orth(const double* p, int64_t m, int32_t s, double ref_norm, double tau,
   const size_t sq = (size_t)s * s * 8, sqa = (sq + 255) / 256 * 256;
   char* w = static_cast<char*>(workspace);
   double* ref = reinterpret_cast<double*>(w);
-  SmallBufs sb{};
-  sb.gram = reinterpret_cast<double*>(w + 256);
-  sb.tmat = reinterpret_cast<double*>(w + 256 + sqa);
-  sb.hmat = reinterpret_cast<double*>(w + 256 + 2 * sqa);
-  sb.splitk = reinterpret_cast<double*>(w + 256 + 3 * sqa);
-  sb.splitk_bytes = 15 * sq;
   char* tail = w + 256 + 3 * sqa + (15 * sq + 255) / 256 * 256;
-  double* tmp = reinterpret_cast<double*>(tail);
-  double* pw = reinterpret_cast<double*>(tail + ((size_t)m * s * 8 + 255) / 256 * 256);
-  int* k1 = reinterpret_cast<int*>(pw + (size_t)m * s);
-  sb.counter = k1 + 16;
-  sb.vecs = sb.gram;  // projection buffers are unused without a previous basis
+  const size_t msb = ((size_t)m * s * 8 + 255) / 256 * 256;
+  OrthArgs a;
+  a.m = m; a.s = s; a.coef = tau * tau; a.ref = ref;
+  a.big = orth_big_rows(m);
+  a.gsum = reinterpret_cast<double*>(w + 256);
+  // partials: 15 s x s matrices and the first m x s buffer behind them; U is the second one
+  a.part = reinterpret_cast<double*>(w + 256 + 3 * sqa);
+  a.part_bytes = (size_t)(tail - (w + 256 + 3 * sqa)) + (size_t)m * s * 8;
+  a.U = reinterpret_cast<double*>(tail + msb); a.ldu = s;
+  a.kept1 = reinterpret_cast<int*>(a.U + (size_t)m * s); a.kept2 = kept;
+  a.Qout = q; a.ldqo = s; a.st = st;
   TTR_CHECK(set_scalar(ref, ref_norm * ref_norm, st));
-  TTR_CHECK(orth_reset_counter(sb.counter, st));
-  return orth_block(p, pw, m, s, ref, tau * tau, q, s, tmp, k1, kept, sb, st);
+  TTR_CHECK(orth_step(a, p, s));
+  return TTR_OK;
 }
 
 int ttr_gram(const void* a, int32_t a_dtype, int64_t m, int64_t n, double* gm, void* workspace,
