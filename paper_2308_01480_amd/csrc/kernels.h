@@ -154,6 +154,8 @@ hipError_t convert_pad(const void* in, int idt, int64_t rows, int cols, int64_t 
 hipError_t symmetrize(double* a, int n, hipStream_t st);
 hipError_t set_scalar(double* p, double v, hipStream_t st);  // *p = v (device)
 hipError_t identity(double* a, int64_t m, hipStream_t st);
+// C (m x n) = A (m x k) B (k x n), float64 row-major, k <= 64 (tt_error.hip).
+hipError_t tt_right_product(int64_t m, int k, int64_t n, const double* A, const double* B, double* C, hipStream_t st);
 // Streaming TT reconstruction error (tt_error.hip): at most part_groups partial triples (at
 // least one per 64 outer rows) in `part`, then out3.
 hipError_t tt_error_blocks(const void* x, int xdt, int64_t outer, int64_t inner, int s_split,

@@ -458,8 +458,7 @@ hipError_t tt_error_run(const void* x, int x_dtype, int d, const int64_t* dims, 
   int which = 0;
   for (int k = d - 2; k >= s; --k) {
     double* out = buf[which];
-    hipError_t e = gemm_nn(ranks[k] * dims[k], (int)ranks[k + 1], (int)rest, cores[k], TTR_F64, ranks[k + 1], R,
-                           rest, 1.0, 0.0, out, rest, st);
+    hipError_t e = tt_right_product(ranks[k] * dims[k], (int)ranks[k + 1], rest, cores[k], R, out, st);
     if (e != hipSuccess) return e;
     rest *= dims[k];
     R = out;

@@ -210,6 +210,46 @@ __global__ __launch_bounds__(256) void k_tt_error_finish(const double* __restric
   if (tid == 0) { out3[0] = r0[0]; out3[1] = r1[0]; out3[2] = r2[0]; }
 }
 
+// C (m x n) = A (m x k) B (k x n) row-major float64, k <= 64: the right part R, core by core.
+// A wave forms 16 rows x 64 columns on the matrix cores, a work-group 64 x 64; A and B come
+// straight from L2 (at 48^5 and rank 20: 960 x 20 times 20 x 2304, 18 MB written).  The general
+// small product spent 75 us there on chunks of 128 inner indices, 108 of them padding.
+__global__ __launch_bounds__(256) void k_tt_right(int64_t m, int k, int64_t n, const double* __restrict__ A,
+                                                  const double* __restrict__ B, double* __restrict__ C) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, q = lane >> 4;
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * 16, c0 = (int64_t)blockIdx.y * 64;
+  if (r0 >= m) return;
+  const int64_t row = r0 + j;
+  d4_t acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int k0 = 0; k0 < k; k0 += 4) {
+    const int kk = k0 + q;
+    const double a = (kk < k && row < m) ? A[row * k + kk] : 0.0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int64_t c = c0 + 16 * t + j;
+      const double b = (kk < k && c < n) ? B[(int64_t)kk * n + c] : 0.0;
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[t], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t r = r0 + q + 4 * v, c = c0 + 16 * t + j;
+      if (r < m && c < n) C[r * n + c] = acc[t][v];
+    }
+}
+
+hipError_t tt_right_product(int64_t m, int k, int64_t n, const double* A, const double* B, double* C, hipStream_t st) {
+  const int64_t gx = (m + 63) / 64, gy = (n + 63) / 64;  // n <= 2^20: an inner block
+  if (m <= 0 || n <= 0 || k <= 0 || gx > INT32_MAX || gy > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_tt_right, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, m, k, n, A, B, C);
+  return hipGetLastError();
+}
+
 template <typename TX, int KS>
 static hipError_t launch_tt_error(const TX* x, int64_t outer, int64_t inner, const TTErrArgs& args, const double* R,
                                   double* part, int64_t part_groups, double* out3, hipStream_t st) {
