@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libttrbki.so")
 SOURCES = ["plan.cpp", "stream_kernels.hip", "bf16_kernels.hip", "small_kernels.hip", "sweep.hip", "grad.hip", "block_orth.hip", "tt_error.hip",
-           "eig_top.hip"]
+           "eig_top.hip", "fused_kernels.hip"]
 ARCH = "gfx950"
 
 
@@ -30,7 +30,7 @@ def _hipcc() -> str:
 # float64 streaming loops (the wide A^T Z and carry kernels above all) copied their
 # accumulators between AGPRs and VGPRs on every iteration.  The bf16 units measured no
 # better with it.
-VGPR_FORM = {"stream_kernels.hip", "block_orth.hip"}
+VGPR_FORM = {"stream_kernels.hip", "block_orth.hip", "fused_kernels.hip"}
 
 
 def _flags(src: str = ""):

@@ -63,6 +63,15 @@ hipError_t launch_aw_omega_bf16(const StreamArgs& a);
 hipError_t launch_omega(uint64_t seed, int k, int64_t beta0, int64_t nrows, int s, int ldo, void* out,
                         int out_dtype, hipStream_t st);
 hipError_t launch_fused_bf16(const StreamArgs& a);
+// The fused product with Z in registers on eight waves (fused_kernels.hip), and whether its
+// registers suffice for the shape.
+bool fused_r_takes(const StreamArgs& a);
+hipError_t launch_fused_r(const StreamArgs& a);
+// y (m x s, ldy) = the per-group partials (m x S, `stride` apart) summed in a fixed order.
+hipError_t launch_reduce_rows(const float* part, int64_t groups, int64_t stride, int m, int S, int s, double* y, int ldy,
+                              hipStream_t st);
+hipError_t launch_reduce_rows(const double* part, int64_t groups, int64_t stride, int m, int S, int s, double* y, int ldy,
+                              hipStream_t st);
 // Omega_k transposed (S x nrows float32, pitch ldt; rows c >= s zero).
 hipError_t launch_omega_t(uint64_t seed, int k, int64_t nrows, int s, int S, int64_t ldt, float* out, hipStream_t st);
 // bfloat16 A (m_pad <= 256): the float32 carry out = Z^T A (rows < s_out, pitch ldo) and,
