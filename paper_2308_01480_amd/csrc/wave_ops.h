@@ -1,5 +1,5 @@
 // Cross-lane reductions of float64 values inside one 64-lane wavefront (DPP row
-// operations, a 32-lane swizzle and lane reads): no LDS and no barriers.
+// operations and lane reads): no LDS and no barriers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,32 +28,31 @@ __device__ inline double sum16(double v) {
   v += dpp_mov<0x140>(v);  // mirror within 16
   return v;
 }
-__device__ inline double swz16(double v) {  // value of lane ^ 16 (within 32)
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __builtin_amdgcn_ds_swizzle(lo, 0x401F);
-  hi = __builtin_amdgcn_ds_swizzle(hi, 0x401F);
-  return __hiloint2double(hi, lo);
-}
-__device__ inline double sum32(double v) {
-  v = sum16(v);
-  return v + swz16(v);
-}
 __device__ inline double lane_value(double v, int l) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
   return __hiloint2double(hi, lo);
 }
+// Row broadcasts (lane 15 of a row into the next row, lane 31 into the upper half) leave
+// ((row 0 + row 1) + (row 2 + row 3)) of the rows' sums in lane 63.
+template <int CTRL>
+__device__ inline double dpp_row_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
 __device__ inline double sum64(double v) {
-  v = sum32(v);
-  return lane_value(v, 0) + lane_value(v, 32);
+  v = sum16(v);
+  v += dpp_row_bcast<0x142>(v);
+  v += dpp_row_bcast<0x143>(v);
+  return lane_value(v, 63);
 }
 __device__ inline double min64(double v) {
   v = fmin(v, dpp_mov<0xB1>(v));
   v = fmin(v, dpp_mov<0x4E>(v));
   v = fmin(v, dpp_mov<0x141>(v));
   v = fmin(v, dpp_mov<0x140>(v));
-  v = fmin(v, swz16(v));
-  return fmin(lane_value(v, 0), lane_value(v, 32));
+  return fmin(fmin(lane_value(v, 0), lane_value(v, 16)), fmin(lane_value(v, 32), lane_value(v, 48)));
 }
 __device__ inline double max64(double v) { return -min64(-v); }
 }  // namespace ttr
