@@ -34,15 +34,6 @@ constexpr int kTopMaxN = 128;
 constexpr int kTopMaxR = 64;
 constexpr int kTopThreads = 256;
 
-// 1/x to full precision from the hardware estimate and two Newton steps (|x| >= DBL_MIN).
-__device__ inline double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-
 typedef double de_t __attribute__((ext_vector_type(2)));  // (d_i, e_{i-1}^2), the second 0 for i = 0
 
 // Number of eigenvalues of the tridiagonal T below x: sign changes of p_i = det(T_i - x I),

@@ -45,17 +45,6 @@ __device__ inline int wave_argmax_positive(double v) {
   return hit ? __builtin_ctzll(hit) : -1;
 }
 
-// 1/sqrt(x) for x > 0: the hardware estimate refined by three Newton steps (quadratic
-// convergence from the estimate's relative error to float64 rounding level).
-__device__ inline double rsqrt_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double hx = 0.5 * x;
-  r = r * fma(-hx * r, r, 1.5);
-  r = r * fma(-hx * r, r, 1.5);
-  r = r * fma(-hx * r, r, 1.5);
-  return r;
-}
-
 // Shared memory of the work-group factorisations below, beside the SMAX x SMAX matrix
 // Rt that the caller places.
 template <int SMAX>

@@ -325,53 +325,76 @@ hipError_t sym_sum(const double* K, int64_t n, double* S, hipStream_t st) {
 // Out: Mb (w x w) = sym( sum_i v_i u_i^T ), with
 //   v_i = sum_{j >= r resolved} u_j (u_j . ub_i) / (lam_i - lam_j)
 //       + (ub_i - U_res U_res^T ub_i) / lam_i                    (unresolved: lam_j = 0).
-// One work-group; work (w x r) holds the v_i.
-__global__ __launch_bounds__(256) void k_eig_adjoint(const double* __restrict__ U, const double* __restrict__ lam,
-                                                     int w, int r, const double* __restrict__ Ub,
-                                                     const int* __restrict__ nv, double* __restrict__ V,
-                                                     double* __restrict__ Mb) {
-  __shared__ double proj[256];
-  const int tid = threadIdx.x;
-  const int kept = *nv < r ? *nv : r;
-  int nres = 0;
-  while (nres < w && lam[nres] > 0.0) ++nres;
+// k_eig_adjoint_v: one work-group per kept i, v_i to column i of V (w x r); k_eig_adjoint_m: Mb,
+// one thread per entry.  Chains of dependent memory reads bound both.  w = 54, r = 12: one
+// work-group for everything, its columns one after another, took 108 us.
+constexpr int kAdjThreads = 256;
+
+__device__ inline int adj_kept(const int* nv, int r) { return *nv < r ? *nv : r; }
+
+__global__ __launch_bounds__(kAdjThreads) void k_eig_adjoint_v(const double* __restrict__ U,
+                                                               const double* __restrict__ lam, int w, int r,
+                                                               const double* __restrict__ Ub,
+                                                               const int* __restrict__ nv, double* __restrict__ V) {
+  __shared__ double proj[kAdjThreads], coef[kAdjThreads], ub[kAdjThreads];
+  __shared__ uint64_t resolved[kAdjThreads / 64];
+  const int tid = threadIdx.x, i = blockIdx.x;
+  if (i >= adj_kept(nv, r)) return;
+  const uint64_t ball = __ballot(tid < w && lam[tid < w ? tid : 0] > 0.0);
+  if ((tid & 63) == 0) resolved[tid >> 6] = ball;
+  if (tid < w) ub[tid] = Ub[tid * r + i];
+  __syncthreads();
+  int nres = 0;  // leading positive values
+  for (int c = 0; c < kAdjThreads / 64; ++c) {
+    const uint64_t m = resolved[c];
+    if (~m) { nres += __ffsll((unsigned long long)~m) - 1; break; }
+    nres += 64;
+  }
+  const double li = lam[i];
+  if (tid < nres) {  // u_j . ub_i for every resolved j
+    double acc = 0.0;
+#pragma unroll 8
+    for (int l = 0; l < w; ++l) acc += U[l * w + tid] * ub[l];
+    proj[tid] = acc;
+    coef[tid] = tid >= r ? acc / (li - lam[tid]) : 0.0;
+  }
+  __syncthreads();
+  if (tid < w) {
+    double res = ub[tid], v = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < nres; ++j) {
+      const double uj = U[tid * w + j];
+      res -= uj * proj[j];
+      v += uj * coef[j];
+    }
+    V[tid * r + i] = v + res / li;
+  }
+}
+
+// Mb = sym(V U_kept^T)
+__global__ __launch_bounds__(kAdjThreads) void k_eig_adjoint_m(const double* __restrict__ U, int w, int r,
+                                                               const int* __restrict__ nv,
+                                                               const double* __restrict__ V, double* __restrict__ Mb) {
+  const int e = blockIdx.x * kAdjThreads + threadIdx.x;
+  if (e >= w * w) return;
+  const int a = e / w, b = e % w, kept = adj_kept(nv, r);
+  double x = 0.0, y = 0.0;
+#pragma unroll 4
   for (int i = 0; i < kept; ++i) {
-    const double li = lam[i];
-    // coefficients c_j = u_j . ub_i for every resolved j
-    for (int j = tid; j < nres; j += blockDim.x) {
-      double acc = 0.0;
-      for (int l = 0; l < w; ++l) acc += U[l * w + j] * Ub[l * r + i];
-      proj[j] = acc;
-    }
-    __syncthreads();
-    for (int l = tid; l < w; l += blockDim.x) {
-      double res = Ub[l * r + i];
-      double v = 0.0;
-      for (int j = 0; j < nres; ++j) {
-        const double uj = U[l * w + j];
-        res -= uj * proj[j];
-        if (j >= r) v += uj * proj[j] / (li - lam[j]);
-      }
-      V[l * r + i] = v + res / li;
-    }
-    __syncthreads();
+    x += V[a * r + i] * U[b * w + i];
+    y += V[b * r + i] * U[a * w + i];
   }
-  // Mb = sym(V U_kept^T)
-  for (int e = tid; e < w * w; e += blockDim.x) {
-    const int a = e / w, b = e % w;
-    double x = 0.0, y = 0.0;
-    for (int i = 0; i < kept; ++i) {
-      x += V[a * r + i] * U[b * w + i];
-      y += V[b * r + i] * U[a * w + i];
-    }
-    Mb[e] = 0.5 * (x + y);
-  }
+  Mb[e] = 0.5 * (x + y);
 }
 
 hipError_t eig_adjoint(const double* U, const double* lam, int w, int r, const double* Ub, const int* nv, double* V,
                        double* Mb, hipStream_t st) {
-  if (w > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_eig_adjoint, dim3(1), dim3(256), 0, st, U, lam, w, r, Ub, nv, V, Mb);
+  if (w > kAdjThreads) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_eig_adjoint_v, dim3(r), dim3(kAdjThreads), 0, st, U, lam, w, r, Ub, nv, V);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_eig_adjoint_m, dim3((w * w + kAdjThreads - 1) / kAdjThreads), dim3(kAdjThreads), 0, st, U, w, r,
+                     nv, V, Mb);
   return hipGetLastError();
 }
 
@@ -518,8 +541,9 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int rowid[kMaxSmall];   // row of A holding R row j
   __shared__ int remain[kMaxSmall];  // indices not yet eliminated
+  __shared__ int gone[kMaxSmall];    // nonzero: eliminated
   __shared__ int s_piv, s_nrem, rotated;
-  __shared__ double s_d0;
+  __shared__ double s_d;
   __shared__ double norms[kMaxSmall + 1];
   double* A = IN_LDS ? reinterpret_cast<double*>(smem) : work;  // n rows of pitch LDA
   const int tid = threadIdx.x, lane = tid & 63;
@@ -527,7 +551,7 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
     const int i = e / LDA, l = e % LDA;
     A[e] = l < n ? g_in[i * n + l] : 0.0;
   }
-  for (int i = tid; i < n; i += NT) remain[i] = i;
+  for (int i = tid; i < n; i += NT) { remain[i] = i; gone[i] = 0; }
   if (tid == 0) s_nrem = n;
   __syncthreads();
 
@@ -536,52 +560,52 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
   // R_j = S[pv, :] / sqrt(S[pv, pv]) (zero on eliminated columns) and updates the
   // remaining block.  Sum_j R_j^T R_j = G on the resolved part. ----
   int k = 0;
+  double d0 = 0.0;
   for (int j = 0; j < n; ++j) {
     const int nrem = s_nrem;
     if (tid < 64) {  // wave 0: argmax over the remaining diagonal, ties by smaller index
       double best = -1.0;
-      int bi = 1 << 30;
+      int bi = 1 << 30, bt = 0;
       for (int t = lane; t < nrem; t += 64) {
         const int i = remain[t];
         const double d = A[i * LDA + i];
-        if (d > best || (d == best && i < bi)) { best = d; bi = i; }
+        if (d > best || (d == best && i < bi)) { best = d; bi = i; bt = t; }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ob = __shfl_xor(best, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+      const double top = max64(best);
+      int pi = best == top ? bi : 1 << 30;
+      for (int off = 32; off > 0; off >>= 1) pi = min(pi, __shfl_xor(pi, off, 64));
+      if (j == 0) d0 = top;
+      const bool ok = nrem > 0 && top > 0.0 && top > (double)n * 0x1p-52 * d0;
+      if (ok && bi == pi) {  // the lane that holds it
+        remain[bt] = remain[nrem - 1];
+        gone[bi] = 1;
+        rowid[j] = bi;
+        s_nrem = nrem - 1;
       }
       if (lane == 0) {
-        if (j == 0) s_d0 = best;
-        const bool ok = nrem > 0 && best > 0.0 && best > (double)n * 0x1p-52 * (j == 0 ? best : s_d0);
-        s_piv = ok ? bi : -1;
-        if (ok) {
-          rowid[j] = bi;
-          int pos = 0;
-          while (remain[pos] != bi) ++pos;
-          remain[pos] = remain[nrem - 1];
-          s_nrem = nrem - 1;
-        }
+        s_piv = ok ? pi : -1;
+        s_d = top;
       }
     }
     __syncthreads();
     const int pv = s_piv;
     if (pv < 0) break;
     k = j + 1;
-    const double rinv = 1.0 / sqrt(A[pv * LDA + pv]);
+    const double rinv = 1.0 / sqrt(s_d);
     const int nr = s_nrem;
-    __syncthreads();  // everyone has read the pivot before row pv is rewritten
     // R_j: diagonal entry sqrt(d), remaining columns scaled, eliminated columns zero
     for (int l = tid; l < n; l += NT) {
       const double v = A[pv * LDA + l];
-      bool rem_l = (l == pv);
-      for (int t = 0; t < nr && !rem_l; ++t) rem_l = remain[t] == l;
-      A[pv * LDA + l] = rem_l ? v * rinv : 0.0;
+      A[pv * LDA + l] = l == pv || gone[l] == 0 ? v * rinv : 0.0;
     }
     __syncthreads();
-    for (int e = tid; e < nr * nr; e += NT) {
-      const int i = remain[e / nr], l = remain[e % nr];
-      A[i * LDA + l] -= A[pv * LDA + i] * A[pv * LDA + l];
+    for (int t = tid >> 5; t < nr; t += NT / 32) {
+      const int i = remain[t];
+      const double f = A[pv * LDA + i];
+      for (int c = tid & 31; c < nr; c += 32) {
+        const int l = remain[c];
+        A[i * LDA + l] -= f * A[pv * LDA + l];
+      }
     }
     __syncthreads();
   }
@@ -617,12 +641,20 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
 #pragma unroll
         for (int t = 0; t < RPL; ++t) { al += x[t] * x[t]; be += y[t] * y[t]; ga += x[t] * y[t]; }
         al = group_sum(al, G); be = group_sum(be, G); ga = group_sum(ga, G);
-        if (al > 0.0 && be > 0.0 && fabs(ga) > tol * sqrt(al * be)) {
-          const double zeta = (be - al) / (2.0 * ga);
+        // estimates and Newton steps in place of divisions and roots, in the range where they hold
+        const double pr = al * be;
+        const bool wide = pr > 0x1p-960 ? fabs(ga) * rsqrt_nr(pr) > tol : fabs(ga) > tol * sqrt(pr);
+        if (al > 0.0 && be > 0.0 && wide) {
+          const double zeta = fabs(ga) > 0x1p-500 ? (be - al) * rcp_nr(2.0 * ga) : (be - al) / (2.0 * ga);
           double t;
-          if (fabs(zeta) > 1e150) t = 0.5 / zeta;
-          else t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-          const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
+          if (fabs(zeta) > 1e150) {
+            t = 0.5 / zeta;
+          } else {
+            const double z1 = 1.0 + zeta * zeta;
+            t = rcp_nr(fabs(zeta) + z1 * rsqrt_nr(z1));
+            t = zeta >= 0.0 ? t : -t;
+          }
+          const double c = rsqrt_nr(1.0 + t * t), s = c * t;
 #pragma unroll
           for (int u = 0; u < RPL; ++u) { rp[u * G] = c * x[u] - s * y[u]; rq[u * G] = s * x[u] + c * y[u]; }
           mine = 1;
@@ -650,6 +682,7 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
     double s2 = 0.0;
     if (j < k) {
       const double* rj = A + rowid[j] * LDA;
+#pragma unroll 8
       for (int i = 0; i < n; ++i) s2 += rj[i] * rj[i];
     }
     norms[j] = s2;
@@ -658,6 +691,7 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
   for (int j = tid; j < n; j += NT) {
     const double nj = norms[j];
     int rank = 0;
+#pragma unroll 8
     for (int i = 0; i < n; ++i) {
       const double ni = norms[i];
       rank += (ni > nj) || (ni == nj && i < j);
@@ -665,6 +699,7 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
     vals[rank] = nj;
     const double inv = nj > 0.0 ? 1.0 / sqrt(nj) : 0.0;
     const double* rj = A + (j < k ? rowid[j] : 0) * LDA;
+#pragma unroll 8
     for (int i = 0; i < n; ++i) vecs[(int64_t)i * n + rank] = j < k ? rj[i] * inv : 0.0;
   }
 }

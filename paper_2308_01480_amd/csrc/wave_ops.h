@@ -55,4 +55,24 @@ __device__ inline double min64(double v) {
   return fmin(fmin(lane_value(v, 0), lane_value(v, 16)), fmin(lane_value(v, 32), lane_value(v, 48)));
 }
 __device__ inline double max64(double v) { return -min64(-v); }
+// 1/x to full precision from the hardware estimate and two Newton steps (|x| >= DBL_MIN).
+__device__ inline double rcp_nr(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+
+// 1/sqrt(x) for x > 0: the hardware estimate refined by three Newton steps (quadratic
+// convergence from the estimate's relative error to float64 rounding level).
+__device__ inline double rsqrt_nr(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double hx = 0.5 * x;
+  r = r * fma(-hx * r, r, 1.5);
+  r = r * fma(-hx * r, r, 1.5);
+  r = r * fma(-hx * r, r, 1.5);
+  return r;
+}
+
 }  // namespace ttr

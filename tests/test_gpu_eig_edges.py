@@ -61,3 +61,23 @@ TIED = [pytest.param(17, 16, marks=pytest.mark.xfail(
 def test_tied_residual(n, r):
     a, v, lam, kept = solve(n, r, "tied")
     assert np.abs(a @ v - v * lam[kept]).max() <= bound(n, a)
+
+
+@pytest.mark.parametrize("exponent", [-700, -300, 0, 400])
+@pytest.mark.parametrize("n,rank", [(2, 1), (16, 16), (17, 5), (32, 31), (33, 33), (64, 9), (65, 64), (129, 40)])
+def test_jacobi_scales(n, rank, exponent):
+    """The full decomposition at scales where products of two eigenvalues leave the range of float64
+    (the rotations then take divisions and roots), rank-deficient, at the edges of the launch shapes."""
+    rng = np.random.default_rng(n)
+    b = rng.standard_normal((n, rank))
+    g = b @ b.T
+    vecs, vals = tt.sym_eig(torch.from_numpy(np.ldexp(g, exponent)).cuda())
+    v, lam = vecs.cpu().numpy(), np.ldexp(vals.cpu().numpy(), -exponent)
+    ref = np.maximum(np.linalg.eigvalsh(g)[::-1], 0.0)
+    # the bounds of the decomposition: 1e-12 between vectors, 4e-12 sqrt(n) of the largest value for the pairs
+    tol = 4e-12 * np.sqrt(n) * ref[0]
+    assert np.abs(lam - ref).max() <= tol
+    assert np.all(lam[rank:] <= tol)
+    kept = lam > tol
+    assert np.abs(v[:, kept].T @ v[:, kept] - np.eye(kept.sum())).max() <= 1e-12
+    assert np.abs(g @ v[:, kept] - v[:, kept] * lam[kept]).max() <= tol
