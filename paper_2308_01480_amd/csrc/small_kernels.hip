@@ -158,9 +158,22 @@ hipError_t gemm_tn_sym(int64_t m, int k, const double* X, int64_t ldx, const dou
 
 // ----------------------------------------------------------------------------------
 // C = alpha X W + beta C, 16 rows x 16 columns per work-group, one output per thread; the
-// inner dimension in chunks of 128 whose X rows and W block are loaded in one round.
+// inner dimension in chunks of 128 whose X rows and W block are loaded in one round; a chunk
+// ends at the last 16 that hold data.  Latency bounds it (inner sizes of 20 to 54 mostly): with
+// every chunk walked to 128 and the leading columns counted one load after another 7.1 us at
+// 24^5's sizes.
 // ----------------------------------------------------------------------------------
 constexpr int kNnRows = 16, kNnK = 128;
+
+// Number of leading entries of v[0 .. n) that are > 0, by one wave, the same in all of them.
+__device__ inline int leading_positive(const double* __restrict__ v, int n) {
+  const int lane = threadIdx.x & 63;
+  for (int base = 0; base < n; base += 64) {
+    const uint64_t no = ~__ballot(base + lane < n && v[min(base + lane, n - 1)] > 0.0);
+    if (no) return base + __ffsll((unsigned long long)no) - 1;
+  }
+  return n;
+}
 
 // colvals (optional): only the leading columns c with colvals[c] > 0 of W are used, the
 // rest read as zero, and their count goes to *ncols.
@@ -176,26 +189,30 @@ __global__ __launch_bounds__(256) void k_gemm_nn(int64_t m, int ka, int kb, cons
   const int c0 = blockIdx.x * 16;
   int kc = kb;
   if (colvals) {
-    kc = 0;
-    while (kc < kb && colvals[kc] > 0.0) ++kc;
+    kc = leading_positive(colvals, kb);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ncols = kc;
   }
   // four interleaved partial sums (k = 4i + q go to q), added in a fixed order
   double acc4[4] = {0.0, 0.0, 0.0, 0.0};
   for (int k0 = 0; k0 < ka; k0 += kNnK) {
+    const int kn = min(ka - k0, kNnK), groups = (kn + 15) / 16;
+    // X: sixteen columns of sixteen rows per round; W: sixteen rows
 #pragma unroll
-    for (int u = 0; u < kNnRows * kNnK / 256; ++u) {
-      const int e = (int)threadIdx.x + 256 * u;
-      const int rr = e / kNnK, kk = e % kNnK;
-      Xs[rr][kk] = (r0 + rr < m && k0 + kk < ka) ? (double)X[(r0 + rr) * ldx + k0 + kk] : 0.0;
-      const int wk = e >> 4, wc = e & 15;
-      Ws[wk][wc] = (k0 + wk < ka && c0 + wc < kc) ? W[(int64_t)(k0 + wk) * ldw + c0 + wc] : 0.0;
-    }
+    for (int u = 0; u < kNnK / 16; ++u)
+      if (u < groups) {
+        const int kk = 16 * u + tx, wk = 16 * u + ty;
+        Xs[ty][kk] = (r0 + ty < m && kk < kn) ? (double)X[(r0 + ty) * ldx + k0 + kk] : 0.0;
+        Ws[wk][tx] = (wk < kn && c0 + tx < kc) ? W[(int64_t)(k0 + wk) * ldw + c0 + tx] : 0.0;
+      }
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < kNnK; kk += 4)
+    for (int u = 0; u < kNnK / 16; ++u)
+      if (u < groups) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc4[q] = fma(Xs[ty][kk + q], Ws[kk + q][tx], acc4[q]);
+        for (int kk = 16 * u; kk < 16 * u + 16; kk += 4)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc4[q] = fma(Xs[ty][kk + q], Ws[kk + q][tx], acc4[q]);
+      }
     __syncthreads();
   }
   const int c = c0 + tx;
@@ -337,19 +354,11 @@ __global__ __launch_bounds__(kAdjThreads) void k_eig_adjoint_v(const double* __r
                                                                const double* __restrict__ Ub,
                                                                const int* __restrict__ nv, double* __restrict__ V) {
   __shared__ double proj[kAdjThreads], coef[kAdjThreads], ub[kAdjThreads];
-  __shared__ uint64_t resolved[kAdjThreads / 64];
   const int tid = threadIdx.x, i = blockIdx.x;
   if (i >= adj_kept(nv, r)) return;
-  const uint64_t ball = __ballot(tid < w && lam[tid < w ? tid : 0] > 0.0);
-  if ((tid & 63) == 0) resolved[tid >> 6] = ball;
   if (tid < w) ub[tid] = Ub[tid * r + i];
   __syncthreads();
-  int nres = 0;  // leading positive values
-  for (int c = 0; c < kAdjThreads / 64; ++c) {
-    const uint64_t m = resolved[c];
-    if (~m) { nres += __ffsll((unsigned long long)~m) - 1; break; }
-    nres += 64;
-  }
+  const int nres = leading_positive(lam, w);
   const double li = lam[i];
   if (tid < nres) {  // u_j . ub_i for every resolved j
     double acc = 0.0;
