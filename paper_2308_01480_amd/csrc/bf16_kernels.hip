@@ -14,12 +14,10 @@
 #include "common.h"
 #include "kernels.h"
 #include "omega.h"
+#include "stream_tiles.h"
 
 namespace ttr {
 
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16;
 
 constexpr int BT = 64;            // tile columns
@@ -30,16 +28,14 @@ __device__ inline f4_t mma_bf16(const bf8_t& a, const bf8_t& b, f4_t c) {
 }
 __device__ inline bf8_t ld8(const bf16* p) { return *reinterpret_cast<const bf8_t*>(p); }
 __device__ inline f4_t fzero() { return f4_t{0.f, 0.f, 0.f, 0.f}; }
-__device__ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // Register staging of a rows x 64 tile: 8 bf16 (16 bytes) per vector, 8 vectors per row.
 template <int MAXV, int NTH = kThreads>
 struct BTile {
   u4_t v[MAXV];
-  __device__ void fetch(const bf16* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0,
-                        bool aligned) {
+  __device__ void fetch(const bf16* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0) {
     const int nv = rows * 8;
-    const bool full = aligned && (col0 + BT <= n);
+    const bool full = col0 + BT <= n;
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
       const int idx = (int)threadIdx.x + i * NTH;
@@ -50,7 +46,7 @@ struct BTile {
         if (row < m) {
           const bf16* src = A + row * n + col0 + cv * 8;
           if (full) {
-            val = *reinterpret_cast<const u4_t*>(src);
+            val = load16(src);
           } else {
             bf16 tmp[8];
 #pragma unroll
@@ -166,7 +162,6 @@ __global__ __launch_bounds__(kThreads) void kb_fused(const bf16* __restrict__ A,
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
 
   load_zt<S>(Zg, m_pad, tp, Zt);
   f4_t acc2[APW][SB];
@@ -175,12 +170,12 @@ __global__ __launch_bounds__(kThreads) void kb_fused(const bf16* __restrict__ A,
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb) acc2[i][sb] = fzero();
   BTile<2 * APW> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * BT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * BT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(Ar, m_pad);
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * BT, aligned);
+    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * BT);
     static_assert(BT == 16 * kWaves, "one 16-column block of W per wave");
     // Phase 1 without a cross-wave sum: wave w forms W for tile columns [16 w, 16 w + 16)
     // over all rows, and stores it rounded to bf16 into Wt, two columns per 32-bit word.
@@ -287,7 +282,6 @@ __global__ __launch_bounds__(kThreads) void kb_aw(const bf16* __restrict__ A, in
   const int rows = (m_pad - row0) < kAwRows ? (m_pad - row0) : kAwRows;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
   f4_t acc2[APW][SB];
 #pragma unroll
   for (int i = 0; i < APW; ++i)
@@ -298,7 +292,7 @@ __global__ __launch_bounds__(kThreads) void kb_aw(const bf16* __restrict__ A, in
     if (t0 < t1) omega_tile<bf16>(seed, kmode, t0 * BT, BT, n, s, Wt + (t0 & 1) * OT, 1, BRP, threadIdx.x, kThreads);
   }
   BTile<2 * APW> regs;
-  if (t0 < t1) regs.fetch(A, m, n, row0, rows, t0 * BT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, row0, rows, t0 * BT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(Ar, rows);
@@ -311,7 +305,7 @@ __global__ __launch_bounds__(kThreads) void kb_aw(const bf16* __restrict__ A, in
     }
     __syncthreads();
     if (t + 1 < t1) {
-      regs.fetch(A, m, n, row0, rows, (t + 1) * BT, aligned);
+      regs.fetch(A, m, n, row0, rows, (t + 1) * BT);
       if constexpr (OM)
         omega_tile<bf16>(seed, kmode, (t + 1) * BT, BT, n, s, Wt + ((t + 1) & 1) * OT, 1, BRP, threadIdx.x, kThreads);
     }
@@ -337,11 +331,10 @@ __global__ __launch_bounds__(kThreads) void kb_atz(const bf16* __restrict__ A, i
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
   const int nchunks = (m_pad + RC - 1) / RC;
   if (nchunks == 1) load_zt<S>(Zg, m_pad, TP, Zt);
   BTile<MAXV> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad < RC ? m_pad : RC, t0 * BT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad < RC ? m_pad : RC, t0 * BT);
   for (int64_t t = t0; t < t1; ++t) {
     f4_t acc1[SB];
 #pragma unroll
@@ -355,9 +348,9 @@ __global__ __launch_bounds__(kThreads) void kb_atz(const bf16* __restrict__ A, i
       __syncthreads();
       if (c + 1 < nchunks) {
         const int nr0 = (c + 1) * RC;
-        regs.fetch(A, m, n, nr0, (m_pad - nr0) < RC ? (m_pad - nr0) : RC, t * BT, aligned);
+        regs.fetch(A, m, n, nr0, (m_pad - nr0) < RC ? (m_pad - nr0) : RC, t * BT);
       } else if (t + 1 < t1) {
-        regs.fetch(A, m, n, 0, m_pad < RC ? m_pad : RC, (t + 1) * BT, aligned);
+        regs.fetch(A, m, n, 0, m_pad < RC ? m_pad : RC, (t + 1) * BT);
       }
       b_phase1_wave<SB>(Ar, Zt, rows, TP, acc1);
     }
@@ -422,11 +415,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   for (int mb = 0; mb < SB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < (SK2 > 0 ? SK2 : 1); ++nb) yacc[mb][nb] = fzero();
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
   const int nks = m_pad / 32;
   BTile<MAXV> ra, rb;
-  if (t0 < t1) ra.fetch(A, m, n, 0, m_pad, t0 * BT, aligned);
-  if (t0 + 1 < t1) rb.fetch(A, m, n, 0, m_pad, (t0 + 1) * BT, aligned);
+  if (t0 < t1) ra.fetch(A, m, n, 0, m_pad, t0 * BT);
+  if (t0 + 1 < t1) rb.fetch(A, m, n, 0, m_pad, (t0 + 1) * BT);
   bf8_t zb[KS][SB];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
@@ -507,8 +499,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     ra.commit(Ar, m_pad);
     if (t + 1 < t1) rb.commit(Ar1, m_pad);
     __syncthreads();
-    if (t + 2 < t1) ra.fetch(A, m, n, 0, m_pad, (t + 2) * BT, aligned);
-    if (t + 3 < t1) rb.fetch(A, m, n, 0, m_pad, (t + 3) * BT, aligned);
+    if (t + 2 < t1) ra.fetch(A, m, n, 0, m_pad, (t + 2) * BT);
+    if (t + 3 < t1) rb.fetch(A, m, n, 0, m_pad, (t + 3) * BT);
     if (SK2 > 0 && t + 1 < t1) load_om(t + 1, omB);
     tile(t, Ar, omA);
     if (SK2 > 0 && t + 2 < t1) load_om(t + 2, omA);
@@ -550,7 +542,6 @@ __global__ __launch_bounds__(NT) void kb_gram(const bf16* __restrict__ A, int64_
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
   const int MB = m_pad / 16;
   const int npairs = MB * (MB + 1) / 2;
   // block pair i of this wave: p = wave + NW i in the row-major upper triangle of MB x MB
@@ -576,13 +567,13 @@ __global__ __launch_bounds__(NT) void kb_gram(const bf16* __restrict__ A, int64_
     if (t0 < t1) omega_tile<bf16>(seed, kmode, t0 * BT, BT, n, s, Ot + (t0 & 1) * OT, 1, BRP, threadIdx.x, NT);
   }
   BTile<MAXM * 8 / NT, NT> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * BT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * BT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(Ar, m_pad);
     __syncthreads();
     if (t + 1 < t1) {
-      regs.fetch(A, m, n, 0, m_pad, (t + 1) * BT, aligned);
+      regs.fetch(A, m, n, 0, m_pad, (t + 1) * BT);
       if constexpr (SKB > 0)
         omega_tile<bf16>(seed, kmode, (t + 1) * BT, BT, n, s, Ot + ((t + 1) & 1) * OT, 1, BRP, threadIdx.x, NT);
     }
@@ -648,7 +639,7 @@ __device__ __host__ constexpr int gram_sb_op() { return TPI * BT + 8; }
 
 template <int SKB, int TPI, bool GRAM>
 __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64_t n, int m_pad, int64_t g,
-                                    int64_t G, int64_t ntiles, bool aligned, bf16* __restrict__ Ar, bf16* __restrict__ Ot,
+                                    int64_t G, int64_t ntiles, bf16* __restrict__ Ar, bf16* __restrict__ Ot,
                                     float* __restrict__ Ys, uint64_t seed, int kmode, int s, f4_t (&acc)[4][4]) {
   constexpr int SW = kGramSketchWaves;
   constexpr int S = SKB * 16;
@@ -682,7 +673,7 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
   BTile<kGramBigM * 8 / kGramBigThreads, kGramBigThreads> regs[TPI];
   if (kc > 0)
 #pragma unroll
-    for (int u = 0; u < TPI; ++u) regs[u].fetch(A, m, n, 0, rows64, (g * TPI + u) * BT, aligned);
+    for (int u = 0; u < TPI; ++u) regs[u].fetch(A, m, n, 0, rows64, (g * TPI + u) * BT);
   for (int64_t k = 0; k < kc; ++k) {
     __syncthreads();
 #pragma unroll
@@ -691,7 +682,7 @@ __device__ inline void gram_sb_loop(const bf16* __restrict__ A, int64_t m, int64
     if (k + 1 < kc) {
       const int64_t jn = g + (k + 1) * G;
 #pragma unroll
-      for (int u = 0; u < TPI; ++u) regs[u].fetch(A, m, n, 0, rows64, (jn * TPI + u) * BT, aligned);
+      for (int u = 0; u < TPI; ++u) regs[u].fetch(A, m, n, 0, rows64, (jn * TPI + u) * BT);
       if constexpr (!GRAM)
         omega_tile<bf16>(seed, kmode, jn * TPI * BT, TPI * BT, n, s, Ot + ((k + 1) & 1) * OT, 1, OP, gtid, gthr);
     }
@@ -752,7 +743,6 @@ __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __rest
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t g = blockIdx.x;
   (void)tiles_per_group;
-  const bool aligned = aligned16(A) && ((n * 2) % 16 == 0);
   const int rows64 = (m_pad + 63) / 64 * 64;
   bf16* Ot = Ar + TPI * rows64 * BRP;                        // SKB > 0: two transposed Omega tiles
   float* Ys = reinterpret_cast<float*>(Ot + 2 * S * gram_sb_op<TPI, SKB>());  // SKB > 0: m_pad x S sketch sums
@@ -762,9 +752,9 @@ __global__ __launch_bounds__(kGramBigThreads) void kb_gram_sb(const bf16* __rest
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = fzero();
   if (SKB == 0 || wave < 10)
-    gram_sb_loop<SKB, TPI, true>(A, m, n, m_pad, g, gridDim.x, ntiles, aligned, Ar, Ot, Ys, seed, kmode, s, acc);
+    gram_sb_loop<SKB, TPI, true>(A, m, n, m_pad, g, gridDim.x, ntiles, Ar, Ot, Ys, seed, kmode, s, acc);
   else
-    gram_sb_loop<SKB, TPI, false>(A, m, n, m_pad, g, gridDim.x, ntiles, aligned, Ar, Ot, Ys, seed, kmode, s, acc);
+    gram_sb_loop<SKB, TPI, false>(A, m, n, m_pad, g, gridDim.x, ntiles, Ar, Ot, Ys, seed, kmode, s, acc);
   if (wave >= 10) return;
   if constexpr (SKB > 0) {
     // each wave copies the sketch tiles it owns (no other wave wrote them)
@@ -845,7 +835,7 @@ __device__ inline void fetch_f32(u4_t (&v)[NV], const float* __restrict__ A, int
     if (rr < rows && row < m) {
       const float* src = A + row * n + col0 + 4 * cv;
       if (full) {
-        val = *reinterpret_cast<const u4_t*>(src);
+        val = load16(src);
       } else {
         float t[4];
 #pragma unroll
@@ -939,14 +929,13 @@ __global__ __launch_bounds__(kThreads) void kb_atz_s(const float* __restrict__ A
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && (n % 4 == 0);
   const int nchunks = (m_pad + RC - 1) / RC;
   u4_t av[AV], zv[ZV];
   auto fetch = [&](int64_t t, int c) {
     const int64_t col0 = t * TC;
     const int row0 = c * RC;
     const int rows = (m_pad - row0) < RC ? (m_pad - row0) : RC;
-    fetch_f32<AV, VPR>(av, A, m, n, row0, rows, col0, aligned && col0 + TC <= n);
+    fetch_f32<AV, VPR>(av, A, m, n, row0, rows, col0, col0 + TC <= n);
     // plane row pc = p S + cc: its RC entries of this chunk are RC / 8 16-byte vectors
 #pragma unroll
     for (int i = 0; i < ZV; ++i) {
@@ -1090,7 +1079,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int rows = (m_pad - row0) < kAwRows ? (m_pad - row0) : kAwRows;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = aligned16(A) && (n % 4 == 0);
   f4_t acc[APW][SB];
 #pragma unroll
   for (int i = 0; i < APW; ++i)
@@ -1102,7 +1090,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   u4_t av[NST][AV], wv[NST][WV];
   auto fetch = [&](int st, int64_t t) {
     const int64_t col0 = t * TT;
-    fetch_f32<AV, VPR>(av[st], A, m, n, row0, rows, col0, aligned && col0 + TT <= n);
+    fetch_f32<AV, VPR>(av[st], A, m, n, row0, rows, col0, col0 + TT <= n);
     if constexpr (WM == 0) {
       const int wrows = (n - col0) < TT ? (int)(n - col0) : TT;
       const u4_t* ws = reinterpret_cast<const u4_t*>(W + col0 * S);
@@ -1121,7 +1109,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         if (idx < 3 * S * (TT / 8)) {
           const bf16* src = Wp + (int64_t)(idx / (TT / 8)) * ldw + col0 + 8 * (idx % (TT / 8));
           if (wfull) {
-            val = *reinterpret_cast<const u4_t*>(src);
+            val = load16(src);
           } else {
             bf16 t8[8];
 #pragma unroll

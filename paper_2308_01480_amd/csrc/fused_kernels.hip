@@ -80,7 +80,6 @@ __global__ __launch_bounds__(kFrThreads, EU) void k_fused_r(const T* __restrict_
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
 
   for (int e = m_pad * AP + threadIdx.x; e < ROWS * AP; e += kFrThreads) As[e] = T(0);
   T zr[KPW][NO];
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(kFrThreads, EU) void k_fused_r(const T* __restrict_
 
   constexpr int VPR = TT * (int)sizeof(T) / 16;
   TileRegs<T, (ROWS * VPR + kFrThreads - 1) / kFrThreads, kFrThreads> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT);
   const int acol = apos((TB == 2 ? 16 * half : 0) + j);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(kFrThreads, EU) void k_fused_r(const T* __restrict_
       }
     }
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT, aligned);
+    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT);
     typename M::acc acc1[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) acc1[o] = M::zero();

@@ -133,7 +133,6 @@ __global__ __launch_bounds__(kThreads) void k_fused(const T* __restrict__ A, int
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
 
   for (int e = threadIdx.x; e < m_pad * S; e += kThreads) Zs[e] = Zg[e];
   typename M::acc acc2[APW][SB];
@@ -143,12 +142,12 @@ __global__ __launch_bounds__(kThreads) void k_fused(const T* __restrict__ A, int
     for (int sb = 0; sb < SB; ++sb) acc2[i][sb] = M::zero();
 
   TileRegs<T, 2 * APW> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(As, m_pad);
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT, aligned);
+    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT);
     typename M::acc acc1[TB][SB];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
@@ -194,7 +193,6 @@ __global__ __launch_bounds__(kZrThreads) void k_fused_zr(const float* __restrict
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(float)) % 16 == 0);
 
   float zr[KPW][SB];
 #pragma unroll
@@ -211,12 +209,12 @@ __global__ __launch_bounds__(kZrThreads) void k_fused_zr(const float* __restrict
     for (int sb = 0; sb < SB; ++sb) acc2[i][sb] = M::zero();
 
   TileRegs<float, (MPK * TT / 4 + kZrThreads - 1) / kZrThreads, kZrThreads, TT> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, MPK, t0 * TT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, MPK, t0 * TT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(As, MPK);
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, MPK, (t + 1) * TT, aligned);
+    if (t + 1 < t1) regs.fetch(A, m, n, 0, MPK, (t + 1) * TT);
     M::acc acc1[SB];
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb) acc1[sb] = M::zero();
@@ -293,7 +291,9 @@ __global__ __launch_bounds__(kZrThreads) void k_fused_zr(const float* __restrict
 // FULL = true: every block [b0, b1) is whole and A, out are 16-byte aligned with n and
 // ldo multiples of VEC, so loads and stores are whole vectors with no column guards (its
 // register footprint stays small enough for four waves per SIMD); FULL = false handles
-// any block with guarded scalar accesses.
+// any block with guarded scalar accesses, in float32 of up to 32 rows the whole blocks by
+// vectors that are aligned to their elements only (24 x 3000001: 134 -> 112 us; the second
+// path's registers cost more than it saves at 60 rows, 91 -> 100 us, and in float64).
 template <typename T, int SB, int KS, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_carry_small(const T* __restrict__ A, int64_t m, int64_t n, int m_pad,
                                                           const T* __restrict__ Zg, T* __restrict__ out, int64_t ldo,
@@ -312,14 +312,15 @@ __global__ __launch_bounds__(kThreads) void k_carry_small(const T* __restrict__ 
   const int64_t nw = (int64_t)gridDim.x * kWaves;
   for (int64_t blk = b0 + (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); blk < b1; blk += nw) {
     const int64_t col = blk * CB + VEC * j;
+    const bool whole = FULL || (sizeof(T) == 4 && KS <= 8 && (blk + 1) * CB <= n);
     T av[KS][VEC];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int64_t row = 4 * ks + q;
-      if (FULL) {
+      if (whole) {
         // rows beyond m read row m - 1 and are zeroed after the load (no divergent load)
         const int64_t rc = row < m ? row : m - 1;
-        u4_t v = *reinterpret_cast<const u4_t*>(A + rc * n + col);
+        u4_t v = FULL ? *reinterpret_cast<const u4_t*>(A + rc * n + col) : load16(A + rc * n + col);
         if (row >= m) v = u4_t{0u, 0u, 0u, 0u};
         *reinterpret_cast<u4_t*>(av[ks]) = v;
       } else {
@@ -350,6 +351,8 @@ __global__ __launch_bounds__(kThreads) void k_carry_small(const T* __restrict__ 
           T* dst = out + (int64_t)c * ldo + col;
           if (FULL) {
             *reinterpret_cast<u4_t*>(dst) = *reinterpret_cast<u4_t*>(v);
+          } else if (whole) {
+            __builtin_memcpy(dst, v, sizeof(v));
           } else {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
@@ -363,7 +366,8 @@ __global__ __launch_bounds__(kThreads) void k_carry_small(const T* __restrict__ 
 // k_gram_small: per-work-group partial A A^T (upper block pairs, float64).  Lane (i, q)
 // holds row rb*16 + i of 4 consecutive vectors; element e of vector t is the
 // k = q column of product (t, e), for the A and the A^T operand alike.  Blocks [b0, b1);
-// FULL as for k_carry_small.  The group's waves are summed as (w0 + w2) + (w1 + w3).
+// FULL as for k_carry_small, whole float32 blocks by vectors at any number of rows (60 x
+// 1000001: 135 -> 96 us; float64 179 -> 306 us).  The group's waves are summed as (w0 + w2) + (w1 + w3).
 template <typename T, int MB, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_gram_small(const T* __restrict__ A, int64_t m, int64_t n, int m_pad,
                                                          double* __restrict__ part, int64_t b0, int64_t b1) {
@@ -379,16 +383,17 @@ __global__ __launch_bounds__(kThreads) void k_gram_small(const T* __restrict__ A
   const int64_t nw = (int64_t)gridDim.x * kWaves;
   for (int64_t blk = b0 + (int64_t)blockIdx.x * kWaves + wave; blk < b1; blk += nw) {
     const int64_t c0 = blk * CB;
+    const bool whole = FULL || (sizeof(T) == 4 && c0 + CB <= n);
     T av[MB][NT4][VEC];
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
       for (int t = 0; t < NT4; ++t) {
         const int64_t row = rb * 16 + i16, col = c0 + (int64_t)t * 4 * VEC + VEC * q;
-        if (FULL) {
+        if (whole) {
           // rows beyond m read row m - 1 and are zeroed after the load (no divergent load)
           const int64_t rc = row < m ? row : m - 1;
-          u4_t v = *reinterpret_cast<const u4_t*>(A + rc * n + col);
+          u4_t v = FULL ? *reinterpret_cast<const u4_t*>(A + rc * n + col) : load16(A + rc * n + col);
           if (row >= m) v = u4_t{0u, 0u, 0u, 0u};
           *reinterpret_cast<u4_t*>(av[rb][t]) = v;
         } else {
@@ -462,7 +467,6 @@ __global__ __launch_bounds__(kThreads) void k_aw(const T* __restrict__ A, int64_
   const int rows = (m_pad - row0) < kAwRows ? (m_pad - row0) : kAwRows;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
 
   typename M::acc acc2[APW][SB];
 #pragma unroll
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(kThreads) void k_aw(const T* __restrict__ A, int64_
   }
   TileRegs<T, 2 * APW> regs;
   if (t0 < t1) {
-    regs.fetch(A, m, n, row0, rows, t0 * TT, aligned);
+    regs.fetch(A, m, n, row0, rows, t0 * TT);
     if constexpr (OM) omega_tile<T>(seed, kmode, t0 * TT, TT, n, s, Ws + (t0 & 1) * TT * S, S, 1, threadIdx.x, kThreads);
     else wfetch(t0);
   }
@@ -509,7 +513,7 @@ __global__ __launch_bounds__(kThreads) void k_aw(const T* __restrict__ A, int64_
     }
     __syncthreads();
     if (t + 1 < t1) {
-      regs.fetch(A, m, n, row0, rows, (t + 1) * TT, aligned);
+      regs.fetch(A, m, n, row0, rows, (t + 1) * TT);
       if constexpr (OM)
         omega_tile<T>(seed, kmode, (t + 1) * TT, TT, n, s, Ws + ((t + 1) & 1) * TT * S, S, 1, threadIdx.x, kThreads);
       else wfetch(t + 1);
@@ -568,7 +572,6 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
   const int nchunks = (m_pad + kRowChunk - 1) / kRowChunk;
 
   const bool zvec = nchunks > 1 && ptr_aligned16(Zg);
@@ -577,7 +580,7 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
   TileRegs<T, MAXV> regs;
   ZChunkRegs<T, S, kRowChunk> zregs;
   if (t0 < t1) {
-    regs.fetch(A, m, n, 0, m_pad < kRowChunk ? m_pad : kRowChunk, t0 * TT, aligned);
+    regs.fetch(A, m, n, 0, m_pad < kRowChunk ? m_pad : kRowChunk, t0 * TT);
     if (zvec) zregs.fetch(Zg, 0, kRowChunk);
   }
   for (int64_t t = t0; t < t1; ++t) {
@@ -599,10 +602,10 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
       if (c + 1 < nchunks) {
         const int nr0 = (c + 1) * kRowChunk;
         const int nrows = (m_pad - nr0) < kRowChunk ? (m_pad - nr0) : kRowChunk;
-        regs.fetch(A, m, n, nr0, nrows, t * TT, aligned);
+        regs.fetch(A, m, n, nr0, nrows, t * TT);
         if (zvec) zregs.fetch(Zg, nr0, nrows);
       } else if (t + 1 < t1) {
-        regs.fetch(A, m, n, 0, m_pad < kRowChunk ? m_pad : kRowChunk, (t + 1) * TT, aligned);
+        regs.fetch(A, m, n, 0, m_pad < kRowChunk ? m_pad : kRowChunk, (t + 1) * TT);
         if (zvec) zregs.fetch(Zg, 0, kRowChunk);
       }
       phase1_accumulate<T, SB>(As, Zs, rows, acc1);
@@ -657,7 +660,6 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
   const int nchunks = (m_pad + RC - 1) / RC;
   auto chunk_rows = [&](int c) { return (m_pad - c * RC) < RC ? (m_pad - c * RC) : RC; };
   // row split (gridDim.y > 1, short unfoldings): chunks [c0, c1) into partial y of rpart
@@ -671,7 +673,7 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
   TileRegs<T, MAXV, kThreads, TC> regs;
   ZChunkRegs<T, S, RC> zregs;
   if (t0 < t1 && c0 < c1) {
-    regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), t0 * TC, aligned);
+    regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), t0 * TC);
     if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
   }
   // with at most two output tiles per wave, even and odd k-steps go to separate
@@ -694,10 +696,10 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
       if constexpr (!ZRES) zregs.commit(Zs, rows);
       __syncthreads();
       if (c + 1 < c1) {
-        regs.fetch(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC, aligned);
+        regs.fetch(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC);
         if constexpr (!ZRES) zregs.fetch(Zg, (c + 1) * RC, chunk_rows(c + 1));
       } else if (t + 1 < t1) {
-        regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), (t + 1) * TC, aligned);
+        regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), (t + 1) * TC);
         if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
       }
       const T* Zc = ZRES ? Zs + (int64_t)c * RC * S : Zs;
@@ -816,7 +818,6 @@ __global__ __launch_bounds__(NT) void k_gram(const T* __restrict__ A, int64_t m,
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
   const int64_t t1 = t0 + tiles_per_group < ntiles ? t0 + tiles_per_group : ntiles;
-  const bool aligned = ptr_aligned16(A) && ((n * (int64_t)sizeof(T)) % 16 == 0);
   const int MB = m_pad / 16;
   const int npairs = MB * (MB + 1) / 2;
   // block pair i of this wave: p = wave + NW i in the row-major upper triangle of MB x MB
@@ -852,12 +853,12 @@ __global__ __launch_bounds__(NT) void k_gram(const T* __restrict__ A, int64_t m,
     for (int r = 0; r < 4; ++r) acc[i][r] = 0.0;
 
   TileRegs<T, MAXM * TileRegs<T, 1>::VPR / NT, NT> regs;  // m_pad <= MAXM rows per tile
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT, aligned);
+  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.template commit<AP - TT>(As, m_pad);
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT, aligned);
+    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT);
     if constexpr (F64ACC && sizeof(T) == 4) {
       // float32 input: lane q = l / 16 takes columns 8 j + 2 q and 8 j + 2 q + 1 of the tile
       // (one 8-byte load per operand) for k-steps 2 j and 2 j + 1 (the sum over a tile's

@@ -38,10 +38,20 @@ template <> struct Mma<double> {
 
 template <typename T> __device__ __host__ constexpr int tile_cols_t() { return sizeof(T) == 8 ? 16 : 32; }
 
+// Sixteen bytes from a pointer that is aligned to its element only: rows of odd length put
+// every row at another offset, and the vector loads of global memory take any of them.  (Four
+// scalar loads in their place: 378 us for the carry of a 250 x 1000003 float32 unfolding.)
+template <typename T>
+__device__ __forceinline__ u4_t load16(const T* p) {
+  u4_t v;
+  __builtin_memcpy(&v, p, sizeof(v));
+  return v;
+}
+
 // ----------------------------------------------------------------------------------
 // Tile staging.  A tile is `rows` (multiple of 16) x TT columns starting at (row0, col0).
 // fetch() issues the global loads into registers (16-byte vectors when the tile is
-// whole and aligned, guarded scalar loads otherwise); commit() writes them to LDS
+// whole, guarded scalar loads otherwise); commit() writes them to LDS
 // with row pitch TT+1.  Rows >= m and columns >= n are zero.
 // ----------------------------------------------------------------------------------
 template <typename T, int MAXV, int NTH = kThreads, int TTC = tile_cols_t<T>()>
@@ -51,13 +61,12 @@ struct TileRegs {
   static constexpr int VPR = TT / VEC;
   u4_t v[MAXV];
 
-  __device__ void fetch(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0,
-                        bool aligned) {
-    if (aligned && col0 + TT <= n) fetch_full(A, m, n, row0, rows, col0);
-    else fetch_guarded(A, m, n, row0, rows, col0, false);
+  __device__ void fetch(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0) {
+    if (col0 + TT <= n) fetch_full(A, m, n, row0, rows, col0);
+    else fetch_guarded(A, m, n, row0, rows, col0);
   }
 
-  // Whole, 16-byte aligned tile: lane (r, cv) loads rows r, r + RSTEP, ... with one
+  // Whole tile: lane (r, cv) loads rows r, r + RSTEP, ... with one
   // 16-byte vector each; the row stride is uniform, so addresses stay per-lane base +
   // scalar offset.
   __device__ void fetch_full(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0) {
@@ -68,13 +77,12 @@ struct TileRegs {
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
       u4_t val = u4_t{0u, 0u, 0u, 0u};
-      if ((int64_t)i * RSTEP < lim) val = *reinterpret_cast<const u4_t*>(base + (int64_t)i * RSTEP * n);
+      if ((int64_t)i * RSTEP < lim) val = load16(base + (int64_t)i * RSTEP * n);
       v[i] = val;
     }
   }
 
-  __device__ void fetch_guarded(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0,
-                                bool full) {
+  __device__ void fetch_guarded(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0) {
     const int nv = rows * VPR;
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
@@ -85,14 +93,10 @@ struct TileRegs {
         const int64_t row = row0 + rr;
         if (row < m) {
           const T* src = A + row * n + col0 + (int64_t)cv * VEC;
-          if (full) {
-            val = *reinterpret_cast<const u4_t*>(src);
-          } else {
-            T tmp[VEC];
+          T tmp[VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) tmp[e] = (col0 + cv * VEC + e < n) ? src[e] : T(0);
-            val = *reinterpret_cast<u4_t*>(tmp);
-          }
+          for (int e = 0; e < VEC; ++e) tmp[e] = (col0 + cv * VEC + e < n) ? src[e] : T(0);
+          val = *reinterpret_cast<u4_t*>(tmp);
         }
       }
       v[i] = val;
