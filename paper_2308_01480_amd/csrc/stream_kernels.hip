@@ -555,6 +555,19 @@ struct ZChunkRegs {
       if (idx < nv) dst[idx] = v[i];
     }
   }
+  // the blocks of 16 columns of row r permuted by an exclusive or with swz(r)
+  template <class Swz>
+  __device__ void commit_swizzled(T* __restrict__ Zs, int rows, Swz swz) const {
+    const int nv = rows * S / VEC;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int idx = (int)threadIdx.x + i * kThreads;
+      if (idx < nv) {
+        const int rr = idx / (S / VEC), col = idx % (S / VEC) * VEC;
+        *reinterpret_cast<u4_t*>(Zs + rr * S + (col ^ swz(rr))) = v[i];
+      }
+    }
+  }
 };
 
 template <typename T, typename TO, int SB, int OUTMODE, int RC>
@@ -635,13 +648,29 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
 // chunk of A (and of Z) is loaded into registers while the current one is multiplied.
 // Output mode 0: out[beta * ldo + c] (n x S); mode 1: out[c * ldo + beta] for c < s_out
 // (the S x n carry), written through an LDS transpose in whole rows.
+//
+// Rows keep their natural pitch in LDS, so that they are written by whole vectors; the four
+// rows (float64: two at a time) that a product's operand reads start in the same bank then,
+// and their blocks of 16 columns are permuted among themselves instead (wide_swz): a read's
+// 64 values lie in 64 different banks (float64: 32 in 32).
+//
+// HBM bounds it, then the float32 products: 1000 x 200000 with 10 columns 247 us at an odd
+// pitch with each k-step's operands read when it starts (half of the LDS time bank conflicts),
+// 222 us (3.6 TB/s) now; 8192 x 65536 with 40 columns 762 us before and 750 now, the products
+// busy 57 % of it.  One column tile per work-group in place of several: no change.
 // ----------------------------------------------------------------------------------
 template <typename T> __device__ __host__ constexpr int wide_cols_t() { return sizeof(T) == 8 ? 64 : 128; }
 constexpr int kWideRows = 64;
 // Elements of the A tile's LDS region, which also holds the transposed output tile (mode 1),
 // rounded up to whole 16-byte vectors so that the Z region after it stays aligned.
 __device__ __host__ constexpr int wide_tile_elems(int tc, int S) {
-  return ((kWideRows * (tc + 1) > tc * (S + 1) ? kWideRows * (tc + 1) : tc * (S + 1)) + 7) / 8 * 8;
+  return ((kWideRows * tc > tc * (S + 1) ? kWideRows * tc : tc * (S + 1)) + 7) / 8 * 8;
+}
+// Exclusive or for the columns of row r at a pitch of `pitch` elements (a multiple of 16).
+template <typename T>
+__device__ __forceinline__ int wide_swz(int r, int pitch) {
+  if (sizeof(T) == 8) return pitch % 32 == 0 ? (r & 1) << 4 : 0;
+  return pitch % 64 == 0 ? (r & 3) << 4 : pitch % 32 == 0 ? (r & 2) << 3 : 0;
 }
 
 template <typename T, typename TO, int SB, int OUTMODE, bool ZRES>
@@ -651,7 +680,7 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
                                                        T* __restrict__ rpart) {
   using M = Mma<T>;
   constexpr int TC = wide_cols_t<T>(), CBW = TC / 16 / kWaves, RC = kWideRows;
-  constexpr int S = SB * 16, AP = TC + 1, WP = S + 1;
+  constexpr int S = SB * 16, WP = S + 1;
   constexpr int MAXV = RC * TC * (int)sizeof(T) / 16 / kThreads;
   extern __shared__ __align__(16) unsigned char smem[];
   T* As = reinterpret_cast<T*>(smem);
@@ -665,10 +694,14 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
   // row split (gridDim.y > 1, short unfoldings): chunks [c0, c1) into partial y of rpart
   const int c0 = (int)blockIdx.y * cps, c1 = c0 + cps < nchunks ? c0 + cps : nchunks;
   const bool split = gridDim.y > 1;
+  const int sa = wide_swz<T>(lane >> 4, TC), sz = wide_swz<T>(lane >> 4, S);  // of rows 4 ks + lane / 16
   if constexpr (ZRES) {
+    constexpr int VEC = 16 / (int)sizeof(T);
     const u4_t* src = reinterpret_cast<const u4_t*>(Zg);
-    u4_t* dst = reinterpret_cast<u4_t*>(Zs);
-    for (int e = threadIdx.x; e < m_pad * S * (int)sizeof(T) / 16; e += kThreads) dst[e] = src[e];
+    for (int e = threadIdx.x; e < m_pad * S / VEC; e += kThreads) {
+      const int rr = e / (S / VEC), col = e % (S / VEC) * VEC;
+      *reinterpret_cast<u4_t*>(Zs + rr * S + (col ^ wide_swz<T>(rr, S))) = src[e];
+    }
   }
   TileRegs<T, MAXV, kThreads, TC> regs;
   ZChunkRegs<T, S, RC> zregs;
@@ -692,8 +725,8 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
     for (int c = c0; c < c1; ++c) {
       const int rows = chunk_rows(c);
       __syncthreads();
-      regs.commit(As, rows);
-      if constexpr (!ZRES) zregs.commit(Zs, rows);
+      regs.commit_swizzled(As, rows, [](int r) { return wide_swz<T>(r, TC); });
+      if constexpr (!ZRES) zregs.commit_swizzled(Zs, rows, [](int r) { return wide_swz<T>(r, S); });
       __syncthreads();
       if (c + 1 < c1) {
         regs.fetch(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC);
@@ -703,23 +736,47 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
         if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
       }
       const T* Zc = ZRES ? Zs + (int64_t)c * RC * S : Zs;
-      // rows is a multiple of 16: an even number of k-steps
-      for (int ks = 0; ks < rows / 4; ks += KH) {
+      // rows is a multiple of 16.  float32: four k-steps at a time, the operands of the next
+      // four read while the products of the present ones run (float64's registers would cost
+      // a third of the waves: 254 -> 371 us for 960 x 110592)
+      constexpr int KU = sizeof(T) == 4 ? 4 : KH;
+      auto read = [&](T (&x)[KU][CBW], T (&y)[KU][SB], int ks) {
 #pragma unroll
-        for (int h = 0; h < KH; ++h) {
+        for (int h = 0; h < KU; ++h) {
           const int row = (ks + h) * 4 + (lane >> 4);
-          T av[CBW], bv[SB];
 #pragma unroll
-          for (int i = 0; i < CBW; ++i) av[i] = As[row * AP + (wave * CBW + i) * 16 + (lane & 15)];
+          for (int i = 0; i < CBW; ++i) x[h][i] = As[row * TC + (((wave * CBW + i) * 16 + (lane & 15)) ^ sa)];
 #pragma unroll
-          for (int sb = 0; sb < SB; ++sb) bv[sb] = Zc[row * S + sb * 16 + (lane & 15)];
+          for (int sb = 0; sb < SB; ++sb) y[h][sb] = Zc[row * S + ((sb * 16 + (lane & 15)) ^ sz)];
+        }
+      };
+      auto multiply = [&](const T (&x)[KU][CBW], const T (&y)[KU][SB]) {
+#pragma unroll
+        for (int h = 0; h < KU; ++h)
 #pragma unroll
           for (int i = 0; i < CBW; ++i)
 #pragma unroll
             for (int sb = 0; sb < SB; ++sb) {
-              if (h == 0) acc[i][sb] = M::mma(av[i], bv[sb], acc[i][sb]);
-              else acch[KH > 1 ? i : 0][KH > 1 ? sb : 0] = M::mma(av[i], bv[sb], acch[KH > 1 ? i : 0][KH > 1 ? sb : 0]);
+              if (h % KH == 0) acc[i][sb] = M::mma(x[h][i], y[h][sb], acc[i][sb]);
+              else acch[KH > 1 ? i : 0][KH > 1 ? sb : 0] = M::mma(x[h][i], y[h][sb], acch[KH > 1 ? i : 0][KH > 1 ? sb : 0]);
             }
+      };
+      const int steps = rows / 4;
+      if constexpr (sizeof(T) == 4) {
+        T av[2][KU][CBW], bv[2][KU][SB];
+        read(av[0], bv[0], 0);
+        for (int ks = 0; ks < steps; ks += 2 * KU) {
+          const bool second = ks + KU < steps;
+          if (second) read(av[1], bv[1], ks + KU);
+          multiply(av[0], bv[0]);
+          if (ks + 2 * KU < steps) read(av[0], bv[0], ks + 2 * KU);
+          if (second) multiply(av[1], bv[1]);
+        }
+      } else {
+        for (int ks = 0; ks < steps; ks += KU) {
+          T av[KU][CBW], bv[KU][SB];
+          read(av, bv, ks);
+          multiply(av, bv);
         }
       }
     }

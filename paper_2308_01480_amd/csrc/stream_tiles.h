@@ -103,6 +103,20 @@ struct TileRegs {
     }
   }
 
+  // Row pitch TT, the blocks of 16 columns of row r permuted by an exclusive or with swz(r).
+  template <class Swz>
+  __device__ void commit_swizzled(T* __restrict__ As, int rows, Swz swz) const {
+    const int nv = rows * VPR;
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+      const int idx = (int)threadIdx.x + i * NTH;
+      if (idx < nv) {
+        const int rr = idx / VPR, col = idx % VPR * VEC;
+        *reinterpret_cast<u4_t*>(As + rr * TT + (col ^ swz(rr))) = v[i];
+      }
+    }
+  }
+
   template <int PAD = 1>
   __device__ void commit(T* __restrict__ As, int rows) const {
     constexpr int AP = TT + PAD;
