@@ -661,10 +661,16 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
 // ----------------------------------------------------------------------------------
 template <typename T> __device__ __host__ constexpr int wide_cols_t() { return sizeof(T) == 8 ? 64 : 128; }
 constexpr int kWideRows = 64;
+// Which instances permute: float32 with 64 columns stays at the odd pitch (128 x 400000: 121 us
+// against 128 permuted).
+template <typename T, int SB>
+__device__ __host__ constexpr bool wide_permutes() { return sizeof(T) == 8 || SB <= 3; }
 // Elements of the A tile's LDS region, which also holds the transposed output tile (mode 1),
 // rounded up to whole 16-byte vectors so that the Z region after it stays aligned.
-__device__ __host__ constexpr int wide_tile_elems(int tc, int S) {
-  return ((kWideRows * tc > tc * (S + 1) ? kWideRows * tc : tc * (S + 1)) + 7) / 8 * 8;
+template <typename T, int SB>
+__device__ __host__ constexpr int wide_tile_elems() {
+  const int tc = wide_cols_t<T>(), rows = kWideRows * (wide_permutes<T, SB>() ? tc : tc + 1), tr = tc * (SB * 16 + 1);
+  return ((rows > tr ? rows : tr) + 7) / 8 * 8;
 }
 // Exclusive or for the columns of row r at a pitch of `pitch` elements (a multiple of 16).
 template <typename T>
@@ -681,10 +687,12 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
   using M = Mma<T>;
   constexpr int TC = wide_cols_t<T>(), CBW = TC / 16 / kWaves, RC = kWideRows;
   constexpr int S = SB * 16, WP = S + 1;
+  constexpr bool SWZ = wide_permutes<T, SB>();
+  constexpr int AP = SWZ ? TC : TC + 1;
   constexpr int MAXV = RC * TC * (int)sizeof(T) / 16 / kThreads;
   extern __shared__ __align__(16) unsigned char smem[];
   T* As = reinterpret_cast<T*>(smem);
-  T* Zs = As + wide_tile_elems(TC, S);
+  T* Zs = As + wide_tile_elems<T, SB>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t g = blockIdx.x;
   const int64_t t0 = g * tiles_per_group;
@@ -694,13 +702,21 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
   // row split (gridDim.y > 1, short unfoldings): chunks [c0, c1) into partial y of rpart
   const int c0 = (int)blockIdx.y * cps, c1 = c0 + cps < nchunks ? c0 + cps : nchunks;
   const bool split = gridDim.y > 1;
-  const int sa = wide_swz<T>(lane >> 4, TC), sz = wide_swz<T>(lane >> 4, S);  // of rows 4 ks + lane / 16
+  // permuted columns of an operand's row 4 ks + lane / 16: blocks of NZ of them repeat, so that
+  // a read is a register and a constant offset (an exclusive or per read took a float64 product
+  // of 64 columns 8% longer)
+  constexpr int NZ = !SWZ || S % 32 != 0 ? 1 : 2;
+  int ca[CBW], cz[NZ];
+#pragma unroll
+  for (int i = 0; i < CBW; ++i) ca[i] = ((wave * CBW + i) * 16 + (lane & 15)) ^ (SWZ ? wide_swz<T>(lane >> 4, TC) : 0);
+#pragma unroll
+  for (int b = 0; b < NZ; ++b) cz[b] = (b * 16 + (lane & 15)) ^ (SWZ ? wide_swz<T>(lane >> 4, S) : 0);
   if constexpr (ZRES) {
     constexpr int VEC = 16 / (int)sizeof(T);
     const u4_t* src = reinterpret_cast<const u4_t*>(Zg);
     for (int e = threadIdx.x; e < m_pad * S / VEC; e += kThreads) {
       const int rr = e / (S / VEC), col = e % (S / VEC) * VEC;
-      *reinterpret_cast<u4_t*>(Zs + rr * S + (col ^ wide_swz<T>(rr, S))) = src[e];
+      *reinterpret_cast<u4_t*>(Zs + rr * S + (SWZ ? col ^ wide_swz<T>(rr, S) : col)) = src[e];
     }
   }
   TileRegs<T, MAXV, kThreads, TC> regs;
@@ -725,8 +741,10 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
     for (int c = c0; c < c1; ++c) {
       const int rows = chunk_rows(c);
       __syncthreads();
-      regs.commit_swizzled(As, rows, [](int r) { return wide_swz<T>(r, TC); });
-      if constexpr (!ZRES) zregs.commit_swizzled(Zs, rows, [](int r) { return wide_swz<T>(r, S); });
+      if constexpr (SWZ) regs.commit_swizzled(As, rows, [](int r) { return wide_swz<T>(r, TC); });
+      else regs.commit(As, rows);
+      if constexpr (!ZRES && SWZ) zregs.commit_swizzled(Zs, rows, [](int r) { return wide_swz<T>(r, S); });
+      if constexpr (!ZRES && !SWZ) zregs.commit(Zs, rows);
       __syncthreads();
       if (c + 1 < c1) {
         regs.fetch(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC);
@@ -736,18 +754,20 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
         if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
       }
       const T* Zc = ZRES ? Zs + (int64_t)c * RC * S : Zs;
-      // rows is a multiple of 16.  float32: four k-steps at a time, the operands of the next
-      // four read while the products of the present ones run (float64's registers would cost
-      // a third of the waves: 254 -> 371 us for 960 x 110592)
-      constexpr int KU = sizeof(T) == 4 ? 4 : KH;
+      // rows is a multiple of 16.  float32 up to 48 columns: four k-steps at a time, the operands
+      // of the next four read while the products of the present ones run.  Elsewhere the
+      // registers would cost a third of the waves: 254 -> 371 us for 960 x 110592 in float64,
+      // 121 -> 156 us for 128 x 400000 with 60 columns in float32.
+      constexpr bool AHEAD = sizeof(T) == 4 && SB <= 3;
+      constexpr int KU = AHEAD ? 4 : KH;
       auto read = [&](T (&x)[KU][CBW], T (&y)[KU][SB], int ks) {
 #pragma unroll
         for (int h = 0; h < KU; ++h) {
           const int row = (ks + h) * 4 + (lane >> 4);
 #pragma unroll
-          for (int i = 0; i < CBW; ++i) x[h][i] = As[row * TC + (((wave * CBW + i) * 16 + (lane & 15)) ^ sa)];
+          for (int i = 0; i < CBW; ++i) x[h][i] = As[row * AP + ca[i]];
 #pragma unroll
-          for (int sb = 0; sb < SB; ++sb) y[h][sb] = Zc[row * S + ((sb * 16 + (lane & 15)) ^ sz)];
+          for (int sb = 0; sb < SB; ++sb) y[h][sb] = Zc[row * S + cz[sb % NZ] + sb / NZ * (16 * NZ)];
         }
       };
       auto multiply = [&](const T (&x)[KU][CBW], const T (&y)[KU][SB]) {
@@ -762,7 +782,7 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
             }
       };
       const int steps = rows / 4;
-      if constexpr (sizeof(T) == 4) {
+      if constexpr (AHEAD) {
         T av[2][KU][CBW], bv[2][KU][SB];
         read(av[0], bv[0], 0);
         for (int ks = 0; ks < steps; ks += 2 * KU) {
@@ -1399,7 +1419,7 @@ static hipError_t launch_atz_wide_t(const StreamArgs& a, void* out, int64_t ldo,
   const int64_t Gu = (ntiles + tpg - 1) / tpg;
   const size_t zbytes = (size_t)a.m_pad * SB * 16 * sizeof(T);
   const bool zres = zbytes <= kWideZResBytes;
-  const size_t lds = (size_t)wide_tile_elems(TC, SB * 16) * sizeof(T) + (zres ? zbytes : (size_t)kWideRows * SB * 16 * sizeof(T));
+  const size_t lds = (size_t)wide_tile_elems<T, SB>() * sizeof(T) + (zres ? zbytes : (size_t)kWideRows * SB * 16 * sizeof(T));
   auto kern = zres ? k_atz_wide<T, TO, SB, OUTMODE, true> : k_atz_wide<T, TO, SB, OUTMODE, false>;
   TTR_HIP(set_lds(kern, lds));
   // Few column tiles (a short, tall unfolding): split the rows over the grid's second
