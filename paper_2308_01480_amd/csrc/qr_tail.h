@@ -106,7 +106,10 @@ __device__ inline void qrcp_block(const double* Gm, int ldg, int s, double thr, 
     const int pv = wave_argmax_positive(diag);
     if (pv < 0) break;
     const double best = lane_value(diag, pv);
-    if (k == 0) floor = fmax(thr, (double)s * 0x1p-52 * best);
+    if (k == 0) {  // the larger of the two; a NaN threshold stays, so that nothing passes it
+      const double low = (double)s * 0x1p-52 * best;
+      floor = thr < low ? low : thr;
+    }
     if (!__builtin_amdgcn_readfirstlane(best > floor)) break;
     double* pb = sm.prow[k & 1];
     if (l == pv) {
