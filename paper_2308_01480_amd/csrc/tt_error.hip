@@ -166,11 +166,20 @@ __global__ __launch_bounds__(256) void k_tt_error(const TX* __restrict__ x, int6
 #pragma unroll
           for (int t = 0; t < VEC; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[ks][t], acc[t], 0, 0, 0);
         }
+        // Beyond the last row / column X is zero and so must Xhat be: the products there are
+        // zeros times entries of a core, which an infinite one turns into NaN.
+        if (!whole || wrow + 16 * rb + 16 > outer) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int t = 0; t < VEC; ++t)
+              if (wrow + 16 * rb + q + 4 * v >= outer || col + t >= inner) acc[t][v] = 0.0;
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
           for (int t = 0; t < VEC; ++t) {
-            const double xv = (double)xr[rb][v][t];  // zero, as Xhat, beyond the last row / column
+            const double xv = (double)xr[rb][v][t];
             const double df = xv - acc[t][v];
             e2 += df * df;
             x2 += xv * xv;
