@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "eig_layout.h"
 #include "kernels.h"
 #include "qr_tail.h"
 #include "wave_ops.h"
@@ -550,7 +551,9 @@ __device__ inline bool any_cluster(const double* __restrict__ lam, int r, double
 
 // Cholesky-QR of the n x r columns of Ys (pitch r + 1), `passes` times: Gram (one thread per
 // entry), Cholesky on four waves (lane l holds row l, each wave a quarter of the columns), then
-// every row of Ys solved against R in registers.  Dependent columns give zeros (rdiag = 0).
+// every row of Ys solved against R in registers.  Dependent columns give zeros (rdiag = 0).  The
+// solve loads RMAX entries from the start of every row of R: the shared memory behind Gm holds
+// them (chol_qr_doubles).
 template <int RMAX>
 __device__ __forceinline__ void chol_qr(int n, int r, int passes, double* __restrict__ Ys, double* __restrict__ Gm,
                                double* __restrict__ Xi, double* __restrict__ rdiag, double (*colx)[64]) {
@@ -727,14 +730,6 @@ __global__ __launch_bounds__(kTopThreads) void k_eig_top(const double* __restric
   __syncthreads();
   eig_top_tail<NB, RMAX>(n, r, bv, gl, dd, ee, de, taus, ReflPacked{Vs, n}, lam, rdiag, colx, twist, inv, Ys, Gm, Xi,
                          SD, SL, SU, vecs, vals);
-}
-
-// Dynamic LDS of k_eig_top: packed reflectors, Y, its Gram / R factor and 1 / R_jj, and bv
-// pairs of twisted factorisations (D, L, U: 3 doubles per entry and vector).
-static size_t eig_top_lds(int n, int r, int bv) {
-  const size_t refl = (size_t)((n * (n - 1) / 2 + 1) & ~1) * 8;
-  const size_t gx = 2 * (size_t)r * (r + 1);
-  return refl + ((size_t)n * (r + 1) + gx) * 8 + (size_t)bv * n * 24 + 16;
 }
 
 template <int NB, int RMAX>
@@ -1145,7 +1140,6 @@ static void tri_lds_plan(int n, int* k0, size_t* bytes) {
 // ----------------------------------------------------------------------------------
 constexpr int kVecPer = 8;
 constexpr int kVecThreads = 256;
-constexpr int kWyPanel = 16;
 constexpr int kWyThreads = 1024;
 constexpr int kWyPairs = kWyPanel * (kWyPanel - 1) / 2;
 
@@ -1328,11 +1322,6 @@ __global__ __launch_bounds__(kWyThreads) void k_back_wy(const double* __restrict
   __syncthreads();
   for (int e = tid; e < n * r; e += kWyThreads) vecs[(int64_t)(e / r) * n + e % r] = Ys[(e / r) * rp + e % r];
   for (int c = tid; c < n; c += kWyThreads) vals[c] = (c < r && rdiag[c] > 0.0 && lam[c] > res0) ? lam[c] : 0.0;
-}
-
-static size_t back_wy_lds(int n, int r) {
-  return ((size_t)n * (r + 1) + (size_t)n * (kWyPanel + 1) + (size_t)kWyPanel * (r + 1) + 2 * (size_t)r * (r + 1)) *
-         sizeof(double);
 }
 
 template <int RMAX>
