@@ -563,6 +563,21 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
   for (int i = tid; i < n; i += NT) { remain[i] = i; gone[i] = 0; }
   if (tid == 0) s_nrem = n;
   __syncthreads();
+  // Products of two eigenvalues leave the range of float64 from about 2^512 (2^-512) on: such a
+  // matrix is scaled by an even power of two, so that its largest diagonal entry is about one.
+  int scale = 0;
+  {
+    double top = 0.0;
+    for (int i = lane; i < n; i += 64) top = fmax(top, A[i * LDA + i]);
+    top = max64(top);
+    if (top < INFINITY) scale = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_exp(top)) / 2 * 2;
+    if (scale > -400 && scale < 400) scale = 0;
+    if (scale != 0) {
+      __syncthreads();  // every wave has read the diagonal
+      for (int e = tid; e < n * LDA; e += NT) A[e] = ldexp(A[e], -scale);
+      __syncthreads();
+    }
+  }
 
   // ---- pivoted Cholesky of the Schur complements, in place and without row swaps:
   // step j picks the remaining index pv with the largest diagonal, turns row pv into
@@ -705,7 +720,7 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
       const double ni = norms[i];
       rank += (ni > nj) || (ni == nj && i < j);
     }
-    vals[rank] = nj;
+    vals[rank] = ldexp(nj, scale);
     const double inv = nj > 0.0 ? 1.0 / sqrt(nj) : 0.0;
     const double* rj = A + (j < k ? rowid[j] : 0) * LDA;
 #pragma unroll 8
