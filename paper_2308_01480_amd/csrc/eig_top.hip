@@ -333,7 +333,7 @@ static int multisect_lanes(int r) {
   return gl;
 }
 
-// lam[j], j = first + (group of this lane) < last: the j-th largest eigenvalue of T by
+// lam[j - first], j = first + (group of this lane) < last: the j-th largest eigenvalue of T by
 // multisection, gl lanes per value counting the eigenvalues below gl interior points.  Groups
 // never straddle a wave: 64 / gl per wave, the last lanes of a wave idle.
 __device__ __forceinline__ void multisect(const de_t* __restrict__ de, int n, const TriBounds& tb, int gl, int first, int last,
@@ -359,7 +359,7 @@ __device__ __forceinline__ void multisect(const de_t* __restrict__ de, int n, co
         lo = nlo;
         hi = nhi;
       }
-      if (g == 0) lam[j] = 0.5 * (lo + hi);
+      if (g == 0) lam[j - first] = 0.5 * (lo + hi);
     }
   }
 }
@@ -370,13 +370,13 @@ __device__ __forceinline__ void multisect(const de_t* __restrict__ de, int n, co
 // |D_k + R_k - (d_k - lambda)|, z_k = 1, z_i = -L_i z_{i+1} (i < k), z_{i+1} = -U_i z_i (i >= k).
 // A value within 1e-3 ||T|| of a neighbour instead takes two solves with L D L^T from a hashed
 // right-hand side, so that the vectors of a cluster span its eigenspace.  Y's column holds R
-// first.  SD, SL, SU: n x bv; twist, inv: cnt entries.
+// first.  lam holds the values from number l0 on; SD, SL, SU: n x bv; twist, inv: cnt entries.
 //
 // What bounds it: chains of n dependent steps per lane, so every loop loads the next four rows
 // before it works on the present ones, zeros that need the three-term relation are looked for
 // by a wave vote, and the final scaling runs on all threads.
 __device__ __forceinline__ void tri_vectors(int n, int r, int j0, int cnt, int bv, const double* __restrict__ dd,
-                                   const double* __restrict__ ee, const double* __restrict__ lam, double nrm,
+                                   const double* __restrict__ ee, const double* __restrict__ lam, int l0, double nrm,
                                    double* __restrict__ Y, int yp, int y0, double* __restrict__ SD,
                                    double* __restrict__ SL, double* __restrict__ SU, int* __restrict__ twist,
                                    double* __restrict__ inv) {
@@ -384,8 +384,9 @@ __device__ __forceinline__ void tri_vectors(int n, int r, int j0, int cnt, int b
   const double tiny = 0x1p-52 * nrm, cthr = 1e-3 * nrm;
   const int t = tid >> 1, side = tid & 1, j = j0 + t, yc = j - y0;
   const bool act = t < cnt && j < r;
-  const double lj = act ? lam[j] : 0.0;
-  const bool clust = act && ((j > 0 && lam[j - 1] - lj < cthr) || (j + 1 < r && lj - lam[j + 1] < cthr));
+  const double lj = act ? lam[j - l0] : 0.0;
+  const bool clust =
+      act && ((j > 0 && lam[j - 1 - l0] - lj < cthr) || (j + 1 < r && lj - lam[j + 1 - l0] < cthr));
   if (act && (side == 0 || !clust)) {
     // both lanes of a pair run the same instructions: side 0 forward (L, D: p = D),
     // side 1 backward (U, R: p = R, R kept in Y)
@@ -648,7 +649,7 @@ __device__ __forceinline__ void eig_top_tail(int n, int r, int bv, int gl, const
   __syncthreads();
   // ---- 3. eigenvectors of T, orthonormalised ----
   const bool any_clust = any_cluster(lam, r, tb.nrm);
-  for (int jb = 0; jb < r; jb += bv) tri_vectors(n, r, jb, bv, bv, dd, ee, lam, tb.nrm, Ys, rp, 0, SD, SL, SU, twist, inv);
+  for (int jb = 0; jb < r; jb += bv) tri_vectors(n, r, jb, bv, bv, dd, ee, lam, 0, tb.nrm, Ys, rp, 0, SD, SL, SU, twist, inv);
   chol_qr<RMAX>(n, r, any_clust ? 2 : 1, Ys, Gm, Xi, rdiag, colx);
   // ---- 4. back-transformation z = Q y with the stored reflectors, last first.  Thread
   //      (row group rg = lane % 16, column group cg = tid / 16) keeps rows rg + 16 a and
@@ -1171,16 +1172,15 @@ __global__ __launch_bounds__(kVecThreads) void k_tri_vectors(double* __restrict_
     const TriBounds tb = tri_bounds(dd, ee, n);
     __syncthreads();
     const int j0 = blockIdx.x * kVecPer, first = max(j0 - 1, 0), last = min(j0 + kVecPer + 1, r);
-    const double* lj = lam - first;  // lam[j - first] is eigenvalue j
-    multisect(de, n, tb, gl, first, last, lam - first);
+    multisect(de, n, tb, gl, first, last, lam);  // lam[j - first] is eigenvalue j
     __syncthreads();
-    tri_vectors(n, r, j0, kVecPer, kVecPer, dd, ee, lj, tb.nrm, Y, kVecPer, j0, SD, SL, SU, twist, inv);
+    tri_vectors(n, r, j0, kVecPer, kVecPer, dd, ee, lam, first, tb.nrm, Y, kVecPer, j0, SD, SL, SU, twist, inv);
     const int nc = min(kVecPer, r - j0);
     for (int e = tid; e < n * nc; e += kVecThreads) {
       const int i = e / nc, c = e - i * nc;
       vecs[(int64_t)i * n + j0 + c] = Y[i * kVecPer + c];
     }
-    if (tid < nc) vals[j0 + tid] = lj[j0 + tid];
+    if (tid < nc) vals[j0 + tid] = lam[j0 + tid - first];
     if (blockIdx.x == 0 && tid == 0) W[(int64_t)(n + 2) * kBigPitch + kBigPitch - 1] = tb.nrm;  // tau_{255} is never used
     return;
   }
