@@ -240,6 +240,15 @@ size_t block_workspace(int64_t m, int64_t n, int cols, int dt);
 
 void set_error(const std::string& msg);
 
+// Rows of Omega (`cols` columns, eight to an item) that one work-group of 256 threads draws: as
+// many as its threads hold items for, and more where the launch would otherwise count 2^32
+// threads, which the runtime refuses.
+inline int64_t omega_rows_per_group(int64_t nrows, int cols) {
+  constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;
+  const int64_t rows = std::max(1, 256 / ((cols + 7) / 8));
+  return std::max(rows, (nrows + kMaxBlocks - 1) / kMaxBlocks);
+}
+
 // Number of column groups a streaming launch uses for ntiles column tiles.
 inline int64_t groups_for(int64_t ntiles, int64_t cap) {
   int64_t g = ntiles < cap ? ntiles : cap;

@@ -997,10 +997,10 @@ __global__ __launch_bounds__(NT) void k_gram(const T* __restrict__ A, int64_t m,
 // ----------------------------------------------------------------------------------
 template <typename TO>
 __global__ __launch_bounds__(256) void k_omega(uint64_t seed, int k, int64_t beta0, int64_t nrows, int s, int ldo,
-                                               int rows_wg, TO* __restrict__ out) {
+                                               int64_t rows_wg, TO* __restrict__ out) {
   const int G8 = (ldo + 7) / 8;
-  // rows_wg rows per work-group (about 256 items): the division by the number of column groups
-  // stays in 32 bits
+  // rows_wg rows per work-group (omega_rows_per_group): the division by the number of column
+  // groups stays in 32 bits
   const int64_t r0 = (int64_t)blockIdx.x * rows_wg;
   for (uint32_t id = threadIdx.x; id < (uint32_t)(rows_wg * G8); id += 256) {
     const uint32_t lr = id / (uint32_t)G8, g = id - lr * (uint32_t)G8;
@@ -1571,7 +1571,7 @@ hipError_t launch_gram_sketch(const StreamArgs& a, double* gm) {
 
 hipError_t launch_omega(uint64_t seed, int k, int64_t beta0, int64_t nrows, int s, int ldo, void* out, int out_dtype,
                         hipStream_t st) {
-  const int rows_wg = std::max(1, 256 / ((ldo + 7) / 8));
+  const int64_t rows_wg = omega_rows_per_group(nrows, ldo);
   const dim3 grid((unsigned)((nrows + rows_wg - 1) / rows_wg));
   if (out_dtype == TTR_F64)
     hipLaunchKernelGGL(k_omega<double>, grid, dim3(256), 0, st, seed, k, beta0, nrows, s, ldo, rows_wg, (double*)out);
