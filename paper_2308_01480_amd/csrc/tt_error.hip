@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void k_tt_right(int64_t m, int k, int64_t n, c
 
 hipError_t tt_right_product(int64_t m, int k, int64_t n, const double* A, const double* B, double* C, hipStream_t st) {
   const int64_t gx = (m + 63) / 64, gy = (n + 63) / 64;  // n <= 2^20: an inner block
-  if (m <= 0 || n <= 0 || k <= 0 || gx > INT32_MAX || gy > 65535) return hipErrorInvalidValue;
+  if (m <= 0 || n <= 0 || k <= 0 || gx >= (1 << 24) || gy > 65535) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_tt_right, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, m, k, n, A, B, C);
   return hipGetLastError();
 }
@@ -285,7 +285,8 @@ static hipError_t launch_tt_error(const TX* x, int64_t outer, int64_t inner, con
   if (want >= 8) want = want / 8 * 8;
   const int64_t chunk = (tiles + want - 1) / want * TC;
   const int64_t nchunks = (inner + chunk - 1) / chunk;
-  if (rblocks * nchunks > part_groups || rblocks * nchunks > INT32_MAX) return hipErrorInvalidValue;
+  // a launch of 2^32 threads is not refused by the runtime, only partly run
+  if (rblocks * nchunks > part_groups || rblocks * nchunks >= (1 << 24)) return hipErrorInvalidValue;
   int rmax = 4 * KS;
   for (int k = 1; k <= args.s; ++k) rmax = std::max(rmax, (int)args.ranks[k]);
   const int pitch = rmax + 1;
