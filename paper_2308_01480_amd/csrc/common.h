@@ -62,7 +62,7 @@ inline int64_t split_w_ld(int64_t n) { return (n + 7) / 8 * 8; }  // row pitch o
 //   bfloat16: row-major A tile pitch TT+8 (the only copy of the tile), transposed Z
 //             and W pitch rows+8 and TT+8; no cross-wave partials (each wave forms W
 //             for its own 16 tile columns).
-inline size_t fused_lds_bytes(int64_t m_pad, int S, int dt) {
+constexpr size_t fused_lds_bytes(int64_t m_pad, int S, int dt) {
   const int tt = tile_cols(dt);
   if (dt == TTR_BF16) return (size_t)m_pad * (tt + 8) * 2 + (size_t)S * (m_pad + 8) * 2 + (size_t)S * (tt + 8) * 2;
   const int b = dtype_bytes(dt);

@@ -28,8 +28,7 @@ constexpr int kFrThreads = 64 * kFrWaves;
 // Pitch of a partial W row: four rows apart (the k-steps' lane groups) fall on distinct banks.
 template <typename T> constexpr int fr_pitch(int S) { return S % 32 == 16 ? S : S + 16; }
 // Vector registers the kernel keeps live: Z, the two products' sums, the tile in flight, and
-// about 36 for operands and addresses.  128 let two work-groups share a CU, 256 one; beyond
-// kFrRegs the form with Z in LDS is taken.
+// about 36 for operands and addresses.  128 let two work-groups share a CU, 256 one.
 template <typename T, int SB, int KPW>
 constexpr int fr_regs() {
   constexpr int words = sizeof(T) / 4, TT = tile_cols_t<T>(), NO = TT == 32 ? SB : (SB + 1) / 2;
@@ -177,9 +176,37 @@ __global__ __launch_bounds__(kFrThreads, EU) void k_fused_r(const T* __restrict_
   }
 }
 
+// Compiled k-steps: rows / 16 rounded up to one of these.
+constexpr int kFrSteps[] = {2, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 32};
+
+// Whether this form takes m_pad rows (a multiple of 16) at the padded width S: one-pass shapes
+// (fused_fits), less those where several work-groups of the form with Z in LDS share a CU and are
+// as fast or faster: float64 while one takes at most half the LDS (112 x 200,000 at 16 columns 53
+// against 69 us, 288 x 331,776 at 32 390 against 366), float32 up to 64 rows (64 x 300,000 at 32
+// 49.4 against 50.6 us, 112 x 200,000 at 16 45.6 against 39.5).
+template <typename T>
+constexpr bool fr_rows(int64_t m_pad, int S) {
+  constexpr int DT = sizeof(T) == 8 ? TTR_F64 : TTR_F32;
+  const size_t z_in_lds = fused_lds_bytes(m_pad, S, DT);
+  if (m_pad > kFusedMaxRows || z_in_lds > kLdsBytes) return false;
+  return DT == TTR_F64 ? z_in_lds > kLdsBytes / 2 : m_pad > 64;
+}
+
+// Whether any of the row counts that KPW k-steps serve is taken.
+template <typename T, int SB, int KPW>
+constexpr bool fr_used() {
+  int below = 0;
+  for (int k : kFrSteps)
+    if (k < KPW) below = k;
+  for (int blocks = below + 1; blocks <= KPW; ++blocks)
+    if (fr_rows<T>(16 * blocks, SB * 16)) return true;
+  return false;
+}
+
 template <typename T, int SB, int KPW>
 static hipError_t launch_fr(const StreamArgs& a) {
-  if constexpr (fr_regs<T, SB, KPW>() <= kFrRegs) {
+  if constexpr (fr_used<T, SB, KPW>()) {
+    static_assert(fr_regs<T, SB, KPW>() <= kFrRegs, "registers");
     constexpr int TT = tile_cols_t<T>(), S = SB * 16;
     constexpr int EU = fr_regs<T, SB, KPW>() <= 128 ? 4 : 2;
     const int64_t ntiles = (a.n + TT - 1) / TT;
@@ -203,69 +230,35 @@ static hipError_t launch_fr(const StreamArgs& a) {
   return hipErrorInvalidValue;
 }
 
-// KPW for m_pad rows: rows / 16 rounded up to a compiled count.
-static int fr_steps(int64_t m_pad) {
-  const int blocks = (int)(m_pad / 16);
-  for (int k : {2, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 32})
-    if (blocks <= k) return k;
-  return 0;
+template <typename T, int SB>
+static hipError_t fr_launch(const StreamArgs& a) {
+  const int blocks = (int)(a.m_pad / 16);
+#define TTR_FR(K) \
+  if (blocks <= K) return launch_fr<T, SB, K>(a);
+  TTR_FR(2) TTR_FR(4) TTR_FR(6) TTR_FR(8) TTR_FR(10) TTR_FR(12) TTR_FR(14) TTR_FR(16) TTR_FR(18) TTR_FR(20) TTR_FR(24)
+  TTR_FR(28) TTR_FR(32)
+#undef TTR_FR
+  return hipErrorInvalidValue;
 }
 
-template <typename T, int SB>
-static bool fr_fits(int kpw) {
-  switch (kpw) {
-#define TTR_FR(K) case K: return fr_regs<T, SB, K>() <= kFrRegs;
-    TTR_FR(2) TTR_FR(4) TTR_FR(6) TTR_FR(8) TTR_FR(10) TTR_FR(12) TTR_FR(14) TTR_FR(16) TTR_FR(18) TTR_FR(20) TTR_FR(24)
-    TTR_FR(28) TTR_FR(32)
-#undef TTR_FR
-  }
-  return false;
-}
-
-template <typename T, int SB>
-static hipError_t fr_launch(const StreamArgs& a, int kpw) {
-  switch (kpw) {
-#define TTR_FR(K) case K: return launch_fr<T, SB, K>(a);
-    TTR_FR(2) TTR_FR(4) TTR_FR(6) TTR_FR(8) TTR_FR(10) TTR_FR(12) TTR_FR(14) TTR_FR(16) TTR_FR(18) TTR_FR(20) TTR_FR(24)
-    TTR_FR(28) TTR_FR(32)
-#undef TTR_FR
+template <typename T>
+static hipError_t fr_width(const StreamArgs& a) {
+  switch (a.S / 16) {
+    case 1: return fr_launch<T, 1>(a);
+    case 2: return fr_launch<T, 2>(a);
+    case 3: return fr_launch<T, 3>(a);
+    case 4: return fr_launch<T, 4>(a);
   }
   return hipErrorInvalidValue;
 }
 
 bool fused_r_takes(const StreamArgs& a) {
-  const int kpw = fr_steps(a.m_pad), SB = a.S / 16;
-  if (a.m_pad > kFusedMaxRows || !kpw) return false;
-  // Where several work-groups of the form with Z in LDS share a CU it is as fast or faster:
-  // float64 while one takes at most half the LDS (112 x 200,000 at 16 columns 53 against 69 us,
-  // 288 x 331,776 at 32 390 against 366), float32 up to 64 rows (64 x 300,000 at 32 49.4
-  // against 50.6 us, 112 x 200,000 at 16 45.6 against 39.5).
-  if (a.dtype == TTR_F64 ? fused_lds_bytes(a.m_pad, a.S, TTR_F64) <= kLdsBytes / 2 : a.m_pad <= 64) return false;
-  if (a.dtype == TTR_F32) return SB == 1 ? fr_fits<float, 1>(kpw) : SB == 2 ? fr_fits<float, 2>(kpw)
-                                 : SB == 3 ? fr_fits<float, 3>(kpw) : SB == 4 && fr_fits<float, 4>(kpw);
-  if (a.dtype == TTR_F64) return SB == 1 ? fr_fits<double, 1>(kpw) : SB == 2 ? fr_fits<double, 2>(kpw)
-                                 : SB == 3 ? fr_fits<double, 3>(kpw) : SB == 4 && fr_fits<double, 4>(kpw);
-  return false;
+  return a.dtype == TTR_F32 ? fr_rows<float>(a.m_pad, a.S) : a.dtype == TTR_F64 && fr_rows<double>(a.m_pad, a.S);
 }
 
 hipError_t launch_fused_r(const StreamArgs& a) {
-  const int kpw = fr_steps(a.m_pad);
-  if (a.dtype == TTR_F32) {
-    switch (a.S / 16) {
-      case 1: return fr_launch<float, 1>(a, kpw);
-      case 2: return fr_launch<float, 2>(a, kpw);
-      case 3: return fr_launch<float, 3>(a, kpw);
-      case 4: return fr_launch<float, 4>(a, kpw);
-    }
-  } else if (a.dtype == TTR_F64) {
-    switch (a.S / 16) {
-      case 1: return fr_launch<double, 1>(a, kpw);
-      case 2: return fr_launch<double, 2>(a, kpw);
-      case 3: return fr_launch<double, 3>(a, kpw);
-      case 4: return fr_launch<double, 4>(a, kpw);
-    }
-  }
-  return hipErrorInvalidValue;
+  if (!fused_r_takes(a)) return hipErrorInvalidValue;
+  return a.dtype == TTR_F32 ? fr_width<float>(a) : fr_width<double>(a);
 }
 
 }  // namespace ttr

@@ -1379,17 +1379,15 @@ template <typename T>
 static hipError_t fused_dispatch(const StreamArgs& a) {
   if (sizeof(T) == 4 && a.m_pad > kFusedMaxRows) return fused_zr_dispatch(a);
   if (fused_r_takes(a)) return launch_fused_r(a);
-  // what is left: float32 of up to 64 rows, or 385 to 512 rows at 64 columns; float64 whose Z and
-  // tile take at most half the LDS
+  // what is left: float32 of up to 64 rows, float64 whose Z and tile take at most half the LDS (272
+  // rows at 16 columns, 160 at 32, 96 at 48, 64 at 64)
   const int SB = a.S / 16;
   const int apw = (int)((a.m_pad / 16 + kWaves - 1) / kWaves);
 #define TTR_F(SBv, APWv) \
   if (SB == SBv && apw <= APWv) return launch_fused_t<T, SBv, APWv>(a);
   TTR_F(1, 1) TTR_F(2, 1) TTR_F(3, 1) TTR_F(4, 1)
-  if constexpr (sizeof(T) == 4) {
-    TTR_F(4, 8)
-  } else {
-    TTR_F(1, 2) TTR_F(2, 2) TTR_F(3, 2) TTR_F(4, 2)
+  if constexpr (sizeof(T) == 8) {
+    TTR_F(1, 2) TTR_F(2, 2) TTR_F(3, 2)
     TTR_F(1, 4) TTR_F(2, 4) TTR_F(1, 6)
   }
 #undef TTR_F
