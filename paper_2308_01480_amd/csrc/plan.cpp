@@ -156,7 +156,9 @@ int make_plan(int32_t d, const int64_t* dims, const int64_t* target_ranks, int32
   int64_t rest = numel;
   int a_dtype = x_dtype;
   size_t max_carry = 0, max_wbuf = 0, max_part = 0, max_zs = 0, max_ms = 0, max_mq = 0, max_mw = 0, max_gram = 0;
-  size_t max_orth_len = 0;  // largest partial of a tall block's orthonormalisation step (doubles)
+  // largest partial of a tall block's orthonormalisation step (doubles): regular modes, and the
+  // r-column block of saturated modes with n < m, which uses the same region where there is one
+  size_t max_orth_len = 0, max_sat_len = 0;
   int max_small = 1;
   int64_t max_m = 1;
   for (int k = 1; k < d; ++k) {
@@ -206,7 +208,10 @@ int make_plan(int32_t d, const int64_t* dims, const int64_t* target_ranks, int32
       }
       if (sh > kMaxSmall) { set_error("saturated short side above 256"); return TTR_EUNSUPPORTED; }
       max_small = std::max<int>(max_small, (int)sh);
-      if (g.m > g.n) max_mw = std::max(max_mw, (size_t)g.m * g.n * 8);
+      if (g.m > g.n) {
+        max_mw = std::max(max_mw, (size_t)g.m * g.n * 8);
+        if (orth_big_rows(g.m)) max_sat_len = std::max(max_sat_len, (size_t)g.r * g.r);
+      }
     }
     P.m[k - 1] = g.m; P.n[k - 1] = g.n; P.s[k - 1] = g.s; P.w[k - 1] = g.w;
     P.kind[k - 1] = g.kind; P.two_pass[k - 1] = g.two_pass; P.gram_first[k - 1] = g.gram_first;
@@ -242,7 +247,8 @@ int make_plan(int32_t d, const int64_t* dims, const int64_t* target_ranks, int32
   L.small_ne = (int)ne;
   L.small_bytes = align256((21 * ne * ne + 3 * kMaxSmall) * 8 + 4096 * 8);
   L.small = off; off = align256(off + L.small_bytes);
-  L.orth_big_bytes = max_orth_len ? align256(((size_t)kOrthBigGroups * (max_orth_len + 1) + 64 * 64) * 8) : 0;
+  const size_t orth_len = max_orth_len ? std::max(max_orth_len, max_sat_len) : 0;
+  L.orth_big_bytes = orth_len ? align256((size_t)kOrthBigGroups * (orth_len + 1) * 8) : 0;
   L.orth_big = off; off = align256(off + L.orth_big_bytes);
   L.total = off;
   P.workspace_bytes = off;
