@@ -141,13 +141,16 @@ __global__ __launch_bounds__(kThreads) void k_fused(const T* __restrict__ A, int
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb) acc2[i][sb] = M::zero();
 
+  // whole tiles laid out first: 64 x 300,000 at 40 columns 70.3 -> 69.2 us in float32 and 110.0 ->
+  // 108.9 in float64, whose 64 columns went from 130.9 to 132
+  constexpr bool WHOLE = sizeof(T) == 4 || SB <= 3;
   TileRegs<T, 2 * APW> regs;
-  if (t0 < t1) regs.fetch(A, m, n, 0, m_pad, t0 * TT);
+  if (t0 < t1) regs.template fetch<WHOLE>(A, m, n, 0, m_pad, t0 * TT);
   for (int64_t t = t0; t < t1; ++t) {
     __syncthreads();
     regs.commit(As, m_pad);
     __syncthreads();
-    if (t + 1 < t1) regs.fetch(A, m, n, 0, m_pad, (t + 1) * TT);
+    if (t + 1 < t1) regs.template fetch<WHOLE>(A, m, n, 0, m_pad, (t + 1) * TT);
     typename M::acc acc1[TB][SB];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
@@ -719,10 +722,14 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
       *reinterpret_cast<u4_t*>(Zs + rr * S + (SWZ ? col ^ wide_swz<T>(rr, S) : col)) = src[e];
     }
   }
+  // whole tiles laid out first: float32 at 64 columns 187.8 -> 183.1 us (960 x 110592; with the
+  // aligned-only loads before 185.7), float64 at 32 with Z in LDS 159.7 -> 155.5 (250 x 200000);
+  // elsewhere no gain or a loss (float64, 8192 x 8192 at 48 columns 450 -> 462)
+  constexpr bool WHOLE = sizeof(T) == 4 ? SB == 4 : SB == 2 && ZRES;
   TileRegs<T, MAXV, kThreads, TC> regs;
   ZChunkRegs<T, S, RC> zregs;
   if (t0 < t1 && c0 < c1) {
-    regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), t0 * TC);
+    regs.template fetch<WHOLE>(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), t0 * TC);
     if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
   }
   // with at most two output tiles per wave, even and odd k-steps go to separate
@@ -747,10 +754,10 @@ __global__ __launch_bounds__(kThreads) void k_atz_wide(const T* __restrict__ A, 
       if constexpr (!ZRES && !SWZ) zregs.commit(Zs, rows);
       __syncthreads();
       if (c + 1 < c1) {
-        regs.fetch(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC);
+        regs.template fetch<WHOLE>(A, m, n, (int64_t)(c + 1) * RC, chunk_rows(c + 1), t * TC);
         if constexpr (!ZRES) zregs.fetch(Zg, (c + 1) * RC, chunk_rows(c + 1));
       } else if (t + 1 < t1) {
-        regs.fetch(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), (t + 1) * TC);
+        regs.template fetch<WHOLE>(A, m, n, (int64_t)c0 * RC, chunk_rows(c0), (t + 1) * TC);
         if constexpr (!ZRES) zregs.fetch(Zg, c0 * RC, chunk_rows(c0));
       }
       const T* Zc = ZRES ? Zs + (int64_t)c * RC * S : Zs;

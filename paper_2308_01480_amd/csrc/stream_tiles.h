@@ -61,8 +61,11 @@ struct TileRegs {
   static constexpr int VPR = TT / VEC;
   u4_t v[MAXV];
 
+  // WHOLE: the compiler is told to expect whole tiles, and lays the loop out for them (results are
+  // the same; which kernels gain by it is measured beside their calls).
+  template <bool WHOLE = false>
   __device__ void fetch(const T* __restrict__ A, int64_t m, int64_t n, int64_t row0, int rows, int64_t col0) {
-    if (col0 + TT <= n) fetch_full(A, m, n, row0, rows, col0);
+    if (WHOLE ? __builtin_expect(col0 + TT <= n, 1) : col0 + TT <= n) fetch_full(A, m, n, row0, rows, col0);
     else fetch_guarded(A, m, n, row0, rows, col0);
   }
 
