@@ -547,6 +547,10 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
   // Rows have pitch LDA = G * RPL >= n and are zero beyond column n, so every lane
   // reads and writes its RPL entries of a row without bounds checks.
   constexpr int LDA = G * RPL;
+  // entries of a row pair that a lane holds at a time: all of them, or a part, read again for the
+  // rotation (both rows of 32 entries were more than the registers of a 1024-thread work-group:
+  // n = 200 55.3 ms with the rest spilled)
+  constexpr int CH = RPL <= 8 ? RPL : 16;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int rowid[kMaxSmall];   // row of A holding R row j
   __shared__ int remain[kMaxSmall];  // indices not yet eliminated
@@ -658,12 +662,20 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
       if (active && p < k && q < k) {
         double* rp = A + rowid[p] * LDA + gl;
         double* rq = A + rowid[q] * LDA + gl;
-        double x[RPL], y[RPL];
-#pragma unroll
-        for (int t = 0; t < RPL; ++t) { x[t] = rp[t * G]; y[t] = rq[t * G]; }
+        double x[CH], y[CH];
         double al = 0.0, be = 0.0, ga = 0.0;
+        auto load = [&](int h) {
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) { al += x[t] * x[t]; be += y[t] * y[t]; ga += x[t] * y[t]; }
+          for (int t = 0; t < CH; ++t) { x[t] = rp[(h + t) * G]; y[t] = rq[(h + t) * G]; }
+        };
+        auto dots = [&] {
+#pragma unroll
+          for (int t = 0; t < CH; ++t) { al += x[t] * x[t]; be += y[t] * y[t]; ga += x[t] * y[t]; }
+        };
+        load(0);
+        dots();
+#pragma unroll 1
+        for (int h = CH; h < RPL; h += CH) { load(h); dots(); }
         al = group_sum(al, G); be = group_sum(be, G); ga = group_sum(ga, G);
         // estimates and Newton steps in place of divisions and roots, in the range where they hold
         const double pr = al * be;
@@ -679,8 +691,15 @@ __global__ __launch_bounds__(NT) void k_eig_psd(const double* __restrict__ g_in,
             t = zeta >= 0.0 ? t : -t;
           }
           const double c = rsqrt_nr(1.0 + t * t), s = c * t;
+#pragma unroll 1
+          for (int h = 0; h < RPL; h += CH) {
+            if (CH < RPL) load(h);
 #pragma unroll
-          for (int u = 0; u < RPL; ++u) { rp[u * G] = c * x[u] - s * y[u]; rq[u * G] = s * x[u] + c * y[u]; }
+            for (int u = 0; u < CH; ++u) {
+              rp[(h + u) * G] = c * x[u] - s * y[u];
+              rq[(h + u) * G] = s * x[u] + c * y[u];
+            }
+          }
           mine = 1;
         }
       }
