@@ -452,9 +452,17 @@ __global__ __launch_bounds__(kThreads) void k_gram_small(const T* __restrict__ A
 // Grid (column group g, row block rb).  With OM the W tile is the sketch's Omega_k,
 // drawn inside the kernel (omega.h) into a double-buffered LDS tile while the previous
 // tile is multiplied, so Omega never reaches HBM (one row block: m_pad <= 256).
+//
+// The launch takes one round of resident work-groups, so the registers of an instance say how many
+// column groups there are and in which order its partials are summed: float32 of 33 to 48 columns
+// with Omega drawn inside needs three waves per SIMD as its neighbours have (at 171 registers, two
+// waves, the sums were a third longer and their error a fifth larger).
 // ----------------------------------------------------------------------------------
+template <typename T, int SB, bool OM>
+constexpr int aw_waves() { return sizeof(T) == 4 && SB == 3 && OM ? 3 : 1; }
+
 template <typename T, int SB, bool OM = false>
-__global__ __launch_bounds__(kThreads) void k_aw(const T* __restrict__ A, int64_t m, int64_t n, int m_pad,
+__global__ __launch_bounds__(kThreads, (aw_waves<T, SB, OM>())) void k_aw(const T* __restrict__ A, int64_t m, int64_t n, int m_pad,
                                                  const T* __restrict__ W, T* __restrict__ part,
                                                  int64_t tiles_per_group, int64_t ntiles, uint64_t seed, int kmode,
                                                  int s) {

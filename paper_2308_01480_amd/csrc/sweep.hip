@@ -33,8 +33,8 @@ struct SmallBufs {
   double* gram;   // Gram / Rayleigh-Ritz matrix
   double* vecs;   // eigenvectors
   double* vals;   // eigenvalues
-  double* tmat;   // SVQB transform, Ritz selection U
-  double* hmat;   // projection coefficients Q_prev^T P
+  double* tmat;   // first transform of an orthonormalisation (taped)
+  double* hmat;   // s x s sums of its separate summing launches
   double* eigw;   // eigen work (n > 128)
   double* splitk; // split-K partials of X^T Y products
   double* scal;   // ||Y_j||_F^2 per block
