@@ -154,7 +154,10 @@ __global__ __launch_bounds__(256) void k_tt_error(const TX* __restrict__ x, int6
           }
         }
       }
-      auto product = [&](int rb, d4_t (&acc)[VEC]) {
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+        if (wrow + 16 * rb >= outer) break;
+        d4_t acc[VEC];
 #pragma unroll
         for (int t = 0; t < VEC; ++t) acc[t] = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -163,13 +166,6 @@ __global__ __launch_bounds__(256) void k_tt_error(const TX* __restrict__ x, int6
 #pragma unroll
           for (int t = 0; t < VEC; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[ks][t], acc[t], 0, 0, 0);
         }
-      };
-      const double before = e2;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        if (wrow + 16 * rb >= outer) break;
-        d4_t acc[VEC];
-        product(rb, acc);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -181,25 +177,25 @@ __global__ __launch_bounds__(256) void k_tt_error(const TX* __restrict__ x, int6
             xinf = fmax(xinf, fabs(acc[t][v]));
           }
       }
-      // Xhat beyond the last row / column is zeros times entries of a core: NaN, not zero, where
-      // an entry is infinite.  Then the tile's errors are summed again without those places.
-      // (A mask in the first sums: 388 to 392 us for 48^5 float32; 383 without any, 385 so.)
-      if ((!whole || wrow + 64 > outer) && __any(e2 != e2)) {
-        e2 = before;
+    }
+    // Xhat beyond the last row / column is zeros times entries of a core: NaN, not zero, where an
+    // entry is infinite.  Then the errors are summed again over the entries that there are.
+    // (Masks in the sums above: 388 to 392 us for 48^5 float32 in place of 382.)
+    if ((inner % (16 * VEC) != 0 || wrow + 64 > outer) && __any(e2 != e2)) {
+      e2 = 0.0;
 #pragma unroll 1
-        for (int rb = 0; rb < 4; ++rb) {
-          d4_t acc[VEC];
-          product(rb, acc);
-          for (int v = 0; v < 4; ++v)
-            for (int t = 0; t < VEC; ++t) {
-              const int64_t row = wrow + 16 * rb + q + 4 * v;
-              if (row < outer && col + t < inner) {
-                const double df = (double)x[row * inner + col + t] - acc[t][v];
-                e2 += df * df;
-              }
-            }
+      for (int64_t c0 = cbeg + (int64_t)16 * VEC * cg; c0 < cend; c0 += (int64_t)16 * VEC * ncg)
+#pragma unroll 1
+        for (int e = 0; e < 16 * VEC; ++e) {
+          const int lr = q + 4 * (e / VEC);
+          const int64_t row = wrow + lr, col = c0 + VEC * j + e % VEC;
+          if (row < outer && col < inner) {
+            double xh = 0.0;
+            for (int k = 0; k < rs; ++k) xh = fma(Lw[lr * pitch + k], R[(int64_t)k * inner + col], xh);
+            const double df = (double)x[row * inner + col] - xh;
+            e2 += df * df;
+          }
         }
-      }
     }
   }
   e2 = sum64(e2);
