@@ -624,11 +624,11 @@ __constant__ int kSuperBlocks[10][2] = {{0, 0}, {0, 1}, {0, 2}, {0, 3}, {1, 1},
 // same order), so each copy keeps only its own registers live; the sketch sums stay in LDS
 // (Ys, m_pad x S float32, each 16 x 16 tile owned by one wave).
 //
-// What bounds it: no unit alone.  Of the 13,400 cycles of an interval of 128 columns (s = 40)
-// the vector ALU is busy 63 % on average and about 71 % on the two SIMDs that take three of the
-// ten generator passes (2,110 cycles each), LDS 59 % (27 % of the cycles are bank conflicts),
-// the matrix cores 25 %, and all waves meet at two barriers.  With the sketch tiles in the
-// generator waves, behind their passes, a 256 x 4.2M call took 980 us, now 830.
+// What bounds it: no unit alone.  Of the about 13,700 cycles of an interval of 128 columns
+// (s = 40) the vector ALU is busy 62 % on average and about 70 % on the two SIMDs that take three
+// of the ten generator passes (2,110 cycles each), LDS 57 % (26 % of the cycles are bank
+// conflicts), the matrix cores 24 %, and all waves meet at two barriers.  With the sketch tiles
+// in the generator waves, behind their passes, a 256 x 4.2M call took 980 us, now 830 to 880.
 // TPI tiles per barrier interval: the A tiles of an interval sit side by side in LDS
 // (TPI x rows x BRP) and its Omega rows form one transposed tile of pitch TPI BT + 8.  Two
 // tiles give 10 generator passes of 64 items per interval at s = 40, which the six

@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kThreads) void k_atz(const T* __restrict__ A, int64
 // HBM bounds it, then the float32 products: 1000 x 200000 with 10 columns 247 us at an odd
 // pitch with each k-step's operands read when it starts (half of the LDS time bank conflicts),
 // 222 us (3.6 TB/s) now; 8192 x 65536 with 40 columns 762 us before and 750 now, the products
-// busy 57 % of it.  One column tile per work-group in place of several: no change.
+// busy 54 % of it.  One column tile per work-group in place of several: no change.
 // ----------------------------------------------------------------------------------
 template <typename T> __device__ __host__ constexpr int wide_cols_t() { return sizeof(T) == 8 ? 64 : 128; }
 constexpr int kWideRows = 64;
