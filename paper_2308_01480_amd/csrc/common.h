@@ -193,7 +193,7 @@ struct Layout {
   size_t small;        // small float64 matrices (Gram, eigenvectors, transforms)
   size_t small_bytes;
   size_t orth_big;     // partials of the tall-block orthonormalisation (0 bytes if unused):
-  size_t orth_big_bytes;  // kOrthBigGroups x w s, then kOrthBigGroups norms
+  size_t orth_big_bytes;  // kOrthBigGroups x w s (r r of a tall saturated mode if more), then kOrthBigGroups norms
   int small_ne;         // side of the square float64 matrices carved from `small`
   size_t total;
 };
